@@ -258,7 +258,7 @@ offt_plan_t offt_plan_ex(int64_t Na, int64_t Nb, int64_t Nc, int dtype, int64_t 
             if (bar != std::string::npos)
                 ok = choice_from_string(fp.substr(bar + 1).c_str(), dtype, rdims, &forced_b);
             else
-                forced_b = default_choice_reversed(dtype, rdims);
+                forced_b = default_choice_reversed(dtype, rdims, batch);
         }
         // a plan string must give the output order the layout asks for
         if (ok && (forced.tax >= 0) != (reversed && reversal_moves_data(dims))) ok = false;
@@ -281,8 +281,8 @@ offt_plan_t offt_plan_ex(int64_t Na, int64_t Nb, int64_t Nc, int dtype, int64_t 
     p->layout = opts.layout;
     hipStream_t s = static_cast<hipStream_t>(opts.stream);
 
-    PlanChoice choice = reversed ? default_choice_reversed(dtype, dims) : default_choice(dtype, dims);
-    PlanChoice choice_b = reversed ? default_choice_reversed(dtype, rdims) : choice;
+    PlanChoice choice = reversed ? default_choice_reversed(dtype, dims, batch) : default_choice(dtype, dims, batch);
+    PlanChoice choice_b = reversed ? default_choice_reversed(dtype, rdims, batch) : choice;
     if (opts.tune == OFFT_TUNE_FORCED) {
         choice = forced;
         choice_b = forced_b;
@@ -351,7 +351,7 @@ offt_plan_t offt_plan_nd(int ndim, const int64_t* dims, int dtype, int64_t batch
         set_error(OFFT_ERR_INVALID_ARG);
         return nullptr;
     }
-    NdChoice choice = default_choice_nd(dtype, ndim, dims);
+    NdChoice choice = default_choice_nd(dtype, ndim, dims, batch);
     if (opts.tune == OFFT_TUNE_FORCED && !nd_choice_from_string(opts.forced_plan, dtype, ndim, dims, &choice)) {
         set_error(OFFT_ERR_BAD_PLAN);
         return nullptr;

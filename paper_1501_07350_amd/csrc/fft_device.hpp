@@ -172,6 +172,131 @@ template <typename V> __device__ __forceinline__ void dft32(V* v) {
     }
 }
 
+template <int R, typename V> __device__ __forceinline__ void dft(V* v);
+
+// Inverse of a modulo m for coprime a, m (index maps of dft_coprime).
+__host__ __device__ constexpr int inverse_mod(int a, int m) {
+    for (int i = 1; i < m; ++i)
+        if ((a * i) % m == 1) return i;
+    return 1;
+}
+
+// R = A * B with coprime A and B (Good's prime-factor algorithm): with
+// n = (B n1 + A n2) mod R, W_R^(n k) = W_A^(n1 k) W_B^(n2 k), so the R-point
+// DFT is an A x B two-dimensional DFT without twiddles; output (k1, k2) is
+// k = k1 mod A, k = k2 mod B.
+template <int A, int B, typename V> __device__ __forceinline__ void dft_coprime(V* v) {
+    constexpr int R = A * B;
+    V t[B][A];
+#pragma unroll
+    for (int n2 = 0; n2 < B; ++n2) {
+#pragma unroll
+        for (int n1 = 0; n1 < A; ++n1) t[n2][n1] = v[(B * n1 + A * n2) % R];
+        dft<A>(t[n2]);
+    }
+    constexpr int KA = B * inverse_mod(B % A, A), KB = A * inverse_mod(A % B, B);
+#pragma unroll
+    for (int k1 = 0; k1 < A; ++k1) {
+        V u[B];
+#pragma unroll
+        for (int n2 = 0; n2 < B; ++n2) u[n2] = t[n2][k1];
+        dft<B>(u);
+#pragma unroll
+        for (int k2 = 0; k2 < B; ++k2) v[(KA * k1 + KB * k2) % R] = u[k2];
+    }
+}
+
+// cos(2 pi k / R) and sin(2 pi k / R) for the inner twiddles W_R^(n2 k1) of
+// dft_square_like (R = 9: exponents up to 4, 25 and 27: up to 16).
+template <int R, typename S> struct InnerRoots;
+template <typename S> struct InnerRoots<9, S> {
+    static __device__ __forceinline__ void get(int e, S* c, S* s) {
+        const S C[5] = {S(1), S(0.766044443118978035202392650555416674), S(0.173648177666930348851716626769314796), S(-0.5),
+                        S(-0.939692620785908384054109277324731470)};
+        const S N[5] = {S(0), S(0.642787609686539326322643409907263433), S(0.984807753012208059366743024589523014),
+                        S(0.866025403784438646763723170752936183), S(0.342020143325668733044099614682259581)};
+        *c = C[e];
+        *s = N[e];
+    }
+};
+template <typename S> struct InnerRoots<25, S> {
+    static __device__ __forceinline__ void get(int e, S* c, S* s) {
+        const S C[17] = {S(1), S(0.968583161128631119490168375464735814), S(0.876306680043863587308115903922062583),
+                         S(0.728968627421411523146730319055259111), S(0.535826794978996618271308767867639978),
+                         S(0.309016994374947424102293417182819059), S(0.062790519529313376076178224565631133),
+                         S(-0.187381314585724630542550734447291469), S(-0.425779291565072648862502445744251704),
+                         S(-0.637423989748689710176712811676016195), S(-0.809016994374947424102293417182819059),
+                         S(-0.929776485888251403660942556221990730), S(-0.992114701314477831049793042785778521),
+                         S(-0.992114701314477831049793042785778521), S(-0.929776485888251403660942556221990730),
+                         S(-0.809016994374947424102293417182819059), S(-0.637423989748689710176712811676016195)};
+        const S N[17] = {S(0), S(0.248689887164854788242283746006447968), S(0.481753674101715274987191502872129654),
+                         S(0.684547105928688673732283357621209270), S(0.844327925502015078548558063966681505),
+                         S(0.951056516295153572116439333379382143), S(0.998026728428271561952336806863450553),
+                         S(0.982287250728688681085641742865268416), S(0.904827052466019527713668647932697594),
+                         S(0.770513242775789230803009636396177847), S(0.587785252292473129168705954639072769),
+                         S(0.368124552684677959156947147492960831), S(0.125333233564304245373118759816508794),
+                         S(-0.125333233564304245373118759816508794), S(-0.368124552684677959156947147492960831),
+                         S(-0.587785252292473129168705954639072769), S(-0.770513242775789230803009636396177847)};
+        *c = C[e];
+        *s = N[e];
+    }
+};
+template <typename S> struct InnerRoots<27, S> {
+    static __device__ __forceinline__ void get(int e, S* c, S* s) {
+        const S C[17] = {S(1), S(0.973044870579823838832885172784695920), S(0.893632640323412248192574186866655117),
+                         S(0.766044443118978035202392650555416674), S(0.597158591702786164851852160583959773),
+                         S(0.396079766039156823696043391609744568), S(0.173648177666930348851716626769314796),
+                         S(-0.058144828910475828538748016847071524), S(-0.286803232711090253103280173167157937),
+                         S(-0.5), S(-0.686241637868733585729604999617537983),
+                         S(-0.835487811412936419653826170019583594), S(-0.939692620785908384054109277324731470),
+                         S(-0.993238357741942988547895552193704340), S(-0.993238357741942988547895552193704340),
+                         S(-0.939692620785908384054109277324731470), S(-0.835487811412936419653826170019583594)};
+        const S N[17] = {S(0), S(0.230615870742440178450198349292939102), S(0.448799180200462172785040334733143616),
+                         S(0.642787609686539326322643409907263433), S(0.802123192755043785083294891933925134),
+                         S(0.918216106880274014758961415314636602), S(0.984807753012208059366743024589523014),
+                         S(0.998308158271268208047820708783277533), S(0.957989512315488874437374766956754624),
+                         S(0.866025403784438646763723170752936183), S(0.727373641573048695987176417663815522),
+                         S(0.549508978070806035262780374050133917), S(0.342020143325668733044099614682259581),
+                         S(0.116092914125230229675666523380711469), S(-0.116092914125230229675666523380711469),
+                         S(-0.342020143325668733044099614682259581), S(-0.549508978070806035262780374050133917)};
+        *c = C[e];
+        *s = N[e];
+    }
+};
+
+// R = A * B with a common factor (9 = 3 x 3, 25 = 5 x 5, 27 = 9 x 3): with
+// n = B n1 + n2 and k = k1 + A k2, the A-point DFTs over n1, the inner
+// twiddles W_R^(n2 k1), then the B-point DFTs over n2.
+template <int A, int B, typename V> __device__ __forceinline__ void dft_square_like(V* v) {
+    using S = decltype(v[0].x);
+    constexpr int R = A * B;
+    V t[B][A];
+#pragma unroll
+    for (int n2 = 0; n2 < B; ++n2) {
+#pragma unroll
+        for (int n1 = 0; n1 < A; ++n1) t[n2][n1] = v[B * n1 + n2];
+        dft<A>(t[n2]);
+    }
+#pragma unroll
+    for (int k1 = 0; k1 < A; ++k1) {
+        V u[B];
+#pragma unroll
+        for (int n2 = 0; n2 < B; ++n2) {
+            if (n2 * k1 == 0) {
+                u[n2] = t[n2][k1];
+            } else {
+                S c, s;
+                InnerRoots<R, S>::get(n2 * k1, &c, &s);
+                u[n2].x = c * t[n2][k1].x + s * t[n2][k1].y;
+                u[n2].y = c * t[n2][k1].y - s * t[n2][k1].x;
+            }
+        }
+        dft<B>(u);
+#pragma unroll
+        for (int k2 = 0; k2 < B; ++k2) v[k1 + A * k2] = u[k2];
+    }
+}
+
 template <int R, typename V> __device__ __forceinline__ void dft(V* v) {
     if constexpr (R == 2) dft2(v[0], v[1]);
     else if constexpr (R == 3) dft3(v);
@@ -180,6 +305,17 @@ template <int R, typename V> __device__ __forceinline__ void dft(V* v) {
     else if constexpr (R == 8) dft8(v);
     else if constexpr (R == 16) dft16(v);
     else if constexpr (R == 32) dft32(v);
+    else if constexpr (R == 9) dft_square_like<3, 3>(v);
+    else if constexpr (R == 25) dft_square_like<5, 5>(v);
+    else if constexpr (R == 27) dft_square_like<9, 3>(v);
+    else if constexpr (R == 6) dft_coprime<2, 3>(v);
+    else if constexpr (R == 10) dft_coprime<2, 5>(v);
+    else if constexpr (R == 12) dft_coprime<4, 3>(v);
+    else if constexpr (R == 15) dft_coprime<5, 3>(v);
+    else if constexpr (R == 18) dft_coprime<2, 9>(v);
+    else if constexpr (R == 20) dft_coprime<4, 5>(v);
+    else if constexpr (R == 24) dft_coprime<8, 3>(v);
+    else if constexpr (R == 30) dft_coprime<6, 5>(v);
     else static_assert(R == 2, "unsupported radix");
 }
 

@@ -7,13 +7,17 @@ variant with radix <= 8 (balanced) and a greedy one (radix-16 stages plus one
 remainder stage), and for 512 and 1024 also two radix-32-sized stages; each
 factor 5 and 3 is its own stage.  Stages
 run largest radix first.  Threads per line = L / (largest radix), so the
-largest-radix stage does one butterfly per thread.
+largest-radix stage does one butterfly per thread.  Beside these come the
+kernels that kernel_defaults.txt names (the measured defaults, with composite
+radices 6 to 30 and other thread counts).
 
 Output: <outdir>/kernels_<prec>_<part>.hip, each holding a slice of the
-instantiations and a table; <outdir>/registry_parts.inc lists the tables.
+instantiations and a table; <outdir>/registry_parts.inc lists the tables and
+<outdir>/kernel_defaults.inc holds kernel_defaults.txt for the planner.
 """
 from __future__ import annotations
 
+import functools
 import os
 import sys
 
@@ -123,13 +127,52 @@ def transposes(seq, P):
 PARTS_MIN_L = 256
 
 
+DEFAULTS = os.path.join(os.path.dirname(os.path.abspath(__file__)), "kernel_defaults.txt")
+
+
+def parse_spec(L, spec):
+    """(radix sequence, threads per line, parts) of a kernel spec
+    "<radices>/<width>[/<threads per line>][/p<parts>]"."""
+    seq_s, _, *rest = spec.split("/")
+    seq = [int(r) for r in seq_s.split("x")]
+    tpl, P = L // max(seq), 1
+    for t in rest:
+        if t.startswith("p"):
+            P = int(t[1:])
+        else:
+            tpl = int(t)
+    return seq, tpl, P
+
+
+@functools.lru_cache(maxsize=None)
+def default_lines():
+    """(precision, line kind, length, specs) of every line of
+    kernel_defaults.txt."""
+    with open(DEFAULTS) as f:
+        rows = [ln.split() for ln in f if ln.strip() and not ln.startswith("#")]
+    return tuple((r[0], r[1], int(r[2]), tuple(r[3:])) for r in rows)
+
+
+def default_entries(prec, L):
+    """Kernels of length L that kernel_defaults.txt names, in file order."""
+    out = []
+    for p, _, n, specs in default_lines():
+        if p == prec and n == L:
+            for s in specs:
+                seq, tpl, P = parse_spec(L, s)
+                if (seq, tpl, P) not in out:
+                    out.append((seq, tpl, P))
+    return out
+
+
 def entries(prec="f64", parts=True):
     """(L, radix sequence, threads per line, parts).  The default thread count
     is L / (largest radix); binary32 kernels of L >= 384 also come with half
     as many threads per line (two largest-radix butterflies per thread), which
     lets a strided tile span 32 columns (256-byte rows) under the thread
     limit.  Kernels of L >= PARTS_MIN_L whose exchanges split also come with
-    2 and 4 parts (strided lines only)."""
+    2 and 4 parts (strided lines only).  Last come the kernels of
+    kernel_defaults.txt."""
     out = []
     for L in lengths():
         for seq in radix_seqs(L):
@@ -142,14 +185,46 @@ def entries(prec="f64", parts=True):
                     if splits(L, seq, P):
                         for t in tpls:
                             out.append((L, seq, t, P))
+        # the measured defaults, where the sequences above do not hold them
+        for seq, t, P in default_entries(prec, L):
+            if (parts or P == 1) and (L, seq, t, P) not in out:
+                out.append((L, seq, t, P))
     return out
+
+
+def legacy(prec, L, seq, tpl, P):
+    """Whether a kernel is one of the radix-sequence rules' (entries without
+    kernel_defaults.txt)."""
+    t0 = L // max(seq)
+    tpls = [t0] + ([t0 // 2] if prec == "f32" and L >= 384 and t0 % 2 == 0 else [])
+    return seq in radix_seqs(L) and tpl in tpls and (P == 1 or (L >= PARTS_MIN_L and P in (2, 4) and splits(L, seq, P)))
+
+
+def emit_defaults(outdir):
+    """kernel_defaults.inc: {dtype, line kind, L, {spec per size class}} rows."""
+    rows = []
+    for prec, kind, L, specs in default_lines():
+        for s in specs:
+            seq, tpl, P = parse_spec(L, s)
+            assert len(specs) == 3 and (P == 1 or (kind != "c" and splits(L, seq, P))), (prec, kind, L, s)
+            assert kind != "t" or transposes(seq, P), (prec, kind, L, s)
+        rows.append(f"    {{{0 if prec == 'f64' else 1}, {'cst'.index(kind)}, {L}, "
+                    f"{{{', '.join(chr(34) + s + chr(34) for s in specs)}}}}},")
+    text = "\n".join(rows) + "\n"
+    path = os.path.join(outdir, "kernel_defaults.inc")
+    if not os.path.exists(path) or open(path).read() != text:
+        with open(path, "w") as f:
+            f.write(text)
 
 
 def emit(outdir):
     os.makedirs(outdir, exist_ok=True)
+    emit_defaults(outdir)
     tables = []
     for prec, vt, dcode in (("f64", "double2", 0), ("f32", "float2", 1)):
         ents = entries(prec)
+        extras = [(L, seq, t, P) for L in lengths() for seq, t, P in default_entries(prec, L)
+                  if not legacy(prec, L, seq, t, P)]
         for part in range(PARTS):
             mine = ents[part::PARTS]
             name = f"kernels_{prec}_{part}"
@@ -189,6 +264,9 @@ def emit(outdir):
                 f"KernelEntry g_{name}[] = {{",
             ]
             for L, seq, tpl, P in mine:
+                # (what kernel_defaults.txt adds is not among the learned
+                # selector's candidates, whose training data it did not have)
+                extra = int((L, seq, tpl, P) in extras)
                 rad = ", ".join(str(x) for x in seq)
                 padded = ", ".join(str(x) for x in (seq + [0] * (8 - len(seq))))
                 # whole-line kernels, and kernels in parts whose first and last
@@ -196,7 +274,7 @@ def emit(outdir):
                 lt = f"&launch_t_one<{L}, {tpl}, {P}, {rad}>" if transposes(seq, P) else "nullptr"
                 mt = max_threads(prec, L, seq, tpl)
                 lines.append(f"    {{{dcode}, {L}, {len(seq)}, {{{padded}}}, {tpl}, {mt}, {P}, "
-                             f"&launch_one<{mt}, {L}, {tpl}, {P}, {rad}>, {lt}}},")
+                             f"&launch_one<{mt}, {L}, {tpl}, {P}, {rad}>, {lt}, {extra}}},")
             lines.append("};")
             lines.append(f"const int g_{name}_n = {len(mine)};")
             lines.append("}  // namespace offt")

@@ -21,7 +21,7 @@ import os
 import sys
 
 sys.path.insert(0, os.path.dirname(os.path.abspath(__file__)))
-from gen_kernels import entries  # noqa: E402
+from gen_kernels import entries, legacy  # noqa: E402
 
 sys.path.pop(0)
 
@@ -40,10 +40,14 @@ CASE_SETS = {"batch": lambda L: L in BATCH_LENGTHS, "all": lambda L: L <= MANY_M
 EXECUTORS = (("batch", "batch", True), ("all", "all", False))
 
 
-def many_cases(prec, which="all"):
-    """Kernel cases (L, radix sequence, threads per line) of one case set."""
+def many_cases(prec, which="all", rules_only=False):
+    """Kernel cases (L, radix sequence, threads per line) of one case set;
+    rules_only: without the kernels that only kernel_defaults.txt names,
+    which the executors do not compile (many-plans choose among the others;
+    with them the work-queue kernel of the batch set, which had twice the
+    cases then, did not come to an end on the GPU)."""
     keep = CASE_SETS[which]
-    return [e[:3] for e in entries(prec, parts=False) if keep(e[0])]
+    return [e[:3] for e in entries(prec, parts=False) if keep(e[0]) and not (rules_only and not legacy(prec, *e))]
 
 
 # waves per SIMD the level-synchronous kernel is compiled for: 4, two
@@ -157,7 +161,7 @@ def emit_many(outdir):
     files = []
     for prec, vt, dcode in PRECISIONS:
         for ex, which, persistent in EXECUTORS:
-            cases = many_cases(prec, which)
+            cases = many_cases(prec, which, rules_only=True)
             files.append(_executor_file(outdir, ex, persistent, prec, vt, dcode, cases))
             if persistent:
                 # in a file of its own: its looped tile code and register

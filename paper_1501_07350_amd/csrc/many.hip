@@ -515,7 +515,8 @@ static int choose_many(offt_plan_s* p, const offt_opts& o) {
         const auto key = std::make_tuple(G.dims[0], G.dims[1], G.dims[2]);
         auto it = chosen.find(key);
         if (it == chosen.end()) {
-            PlanChoice c = default_choice(p->dtype, G.dims);
+            const PlanChoice rules = default_choice(p->dtype, G.dims, 1, true);
+            PlanChoice c = rules;
             if (o.tune == OFFT_TUNE_EXHAUSTIVE || o.tune == OFFT_TUNE_LEARNED) {
                 // tune the shape as a single-grid plan
                 offt_plan_s tmp;
@@ -523,16 +524,23 @@ static int choose_many(offt_plan_s* p, const offt_opts& o) {
                 tmp.dtype = p->dtype;
                 memcpy(tmp.dims, G.dims, sizeof G.dims);
                 tmp.batch = 1;
+                tmp.rules_only = true;
                 offt_opts o2 = o;
                 const int rc = select_plan(&tmp, o2, &c, nullptr);
                 for (void* d : tmp.allocs) (void)hipFree(d);
                 if (rc != OFFT_SUCCESS) return rc;
+                // a plan cache or the selector may name a kernel the executors do not hold
+                for (int ax = 0; ax < 3; ++ax)
+                    if (c.k[ax] && c.k[ax]->extra) {
+                        c.k[ax] = rules.k[ax];
+                        c.logW[ax] = rules.logW[ax];
+                    }
             }
             it = chosen.emplace(key, c).first;
         }
         G.choice = it->second;
         G.ntuned = build_passes(G.choice, G.dims, 1, G.tuned);
-        G.nheur = build_passes(default_choice(p->dtype, G.dims), G.dims, 1, G.heur);
+        G.nheur = build_passes(default_choice(p->dtype, G.dims, 1, true), G.dims, 1, G.heur);
         int rc = attach_twiddles(p, G.tuned, G.ntuned, s);
         if (rc == OFFT_SUCCESS) rc = attach_twiddles(p, G.heur, G.nheur, s);
         if (rc != OFFT_SUCCESS) return rc;

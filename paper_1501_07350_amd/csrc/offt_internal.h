@@ -33,6 +33,7 @@ struct KernelEntry {
     int nparts;                // parts each LDS exchange runs in (> 1: strided lines only)
     LaunchFn launch;
     LaunchFn launch_t;         // the same tile code as a transposing pass, else nullptr
+    int extra;                 // 1: compiled for kernel_defaults.txt only (not a selector candidate)
 };
 
 // One kernel case compiled into the persistent batch executor.
@@ -57,7 +58,7 @@ struct ManyExecutor {
 // Registry of all compiled pass kernels (generated tables).
 const std::vector<const KernelEntry*>& registry();
 // All kernels for (dtype, L), default first.
-std::vector<const KernelEntry*> kernels_for(int dtype, int L);
+const std::vector<const KernelEntry*>& kernels_for(int dtype, int L);
 
 // One axis pass of a plan.
 struct PassPlan {
@@ -176,7 +177,7 @@ struct NdChoice {
 bool nd_slab_fits(const NdChoice& c, const int64_t* dims);
 PassPlan make_pass_nd(int ndim, const int64_t* dims, int64_t batch, int ax, const KernelEntry* k, int logW,
                       int xcd = 0, int io = kIoAuto);
-NdChoice default_choice_nd(int dtype, int ndim, const int64_t* dims);
+NdChoice default_choice_nd(int dtype, int ndim, const int64_t* dims, int64_t batch = 1);
 std::string nd_choice_to_string(const NdChoice& c, const int64_t* dims);
 bool nd_choice_from_string(const char* s, int dtype, int ndim, const int64_t* dims, NdChoice* out,
                            bool check_fit = true);
@@ -188,10 +189,13 @@ std::string choice_to_string(const PlanChoice& c, const int64_t dims[3]);
 // Parses a plan string; returns false if it does not parse or does not fit
 // dims/dtype (with check_fit, also when a tile exceeds this device's limits).
 bool choice_from_string(const char* s, int dtype, const int64_t dims[3], PlanChoice* out, bool check_fit = true);
-PlanChoice default_choice(int dtype, const int64_t dims[3]);
+// Heuristic plan (the kernels depend on the bytes of the whole batch).
+// rules_only: without the kernels that only kernel_defaults.txt names (the
+// batch executors do not hold them).
+PlanChoice default_choice(int dtype, const int64_t dims[3], int64_t batch = 1, bool rules_only = false);
 // Heuristic plan with the output in reversed (cba) order; equal to
 // default_choice when the reversal moves no data.
-PlanChoice default_choice_reversed(int dtype, const int64_t dims[3]);
+PlanChoice default_choice_reversed(int dtype, const int64_t dims[3], int64_t batch = 1);
 // Candidate plans for tuning (deterministic order, default first).
 std::vector<PlanChoice> candidate_choices(int dtype, const int64_t dims[3]);
 // The learned selector's candidate list: candidate_choices, then the

@@ -36,7 +36,8 @@ const std::vector<const KernelEntry*>& registry() {
 // sequences, then fewest stages, then largest leading radix, then the most
 // threads per line (one butterfly of the largest radix per thread), then
 // whole-line exchanges before exchanges in parts.
-std::vector<const KernelEntry*> kernels_for(int dtype, int L) {
+// (Sorted once per length: planning a batch of 64 grids asks hundreds of times.)
+static std::vector<const KernelEntry*> sorted_kernels(int dtype, int L) {
     std::vector<const KernelEntry*> v;
     for (const KernelEntry* e : registry())
         if (e->dtype == dtype && e->L == L) v.push_back(e);
@@ -48,6 +49,18 @@ std::vector<const KernelEntry*> kernels_for(int dtype, int L) {
     std::stable_sort(v.begin(), v.end(),
                      [&](const KernelEntry* x, const KernelEntry* y) { return key(x) < key(y); });
     return v;
+}
+
+const std::vector<const KernelEntry*>& kernels_for(int dtype, int L) {
+    static const auto all = [] {
+        std::vector<std::vector<const KernelEntry*>> t(2 * (OFFT_MAX_AXIS + 1));
+        for (int d : {OFFT_C2C_F64, OFFT_C2C_F32})
+            for (int n = 1; n <= OFFT_MAX_AXIS; ++n) t[(d == OFFT_C2C_F64 ? 0 : OFFT_MAX_AXIS + 1) + n] = sorted_kernels(d, n);
+        return t;
+    }();
+    static const std::vector<const KernelEntry*> none;
+    if (L < 1 || L > OFFT_MAX_AXIS) return none;
+    return all[(dtype == OFFT_C2C_F64 ? 0 : OFFT_MAX_AXIS + 1) + L];
 }
 
 static int default_tpl(const KernelEntry* k) {
@@ -243,15 +256,15 @@ static const KernelEntry* default_kernel(int dtype, int L, bool strided) {
     std::vector<const KernelEntry*> ks;
     if (strided && L >= 512) {
         for (const KernelEntry* k : kernels_for(dtype, L))
-            if (k->nparts == 2 && max_radix(k) >= 32) ks.push_back(k);
+            if (!k->extra && k->nparts == 2 && max_radix(k) >= 32) ks.push_back(k);
         for (const KernelEntry* k : kernels_for(dtype, L))
-            if (k->nparts == 2 && max_radix(k) <= 16) ks.push_back(k);
+            if (!k->extra && k->nparts == 2 && max_radix(k) <= 16) ks.push_back(k);
     }
     if (!strided && dtype == OFFT_C2C_F32)
         for (const KernelEntry* k : kernels_for(dtype, L))
-            if (k->nparts == 1 && max_radix(k) <= 8 && k->tpl * max_radix(k) == L) ks.push_back(k);
+            if (!k->extra && k->nparts == 1 && max_radix(k) <= 8 && k->tpl * max_radix(k) == L) ks.push_back(k);
     for (const KernelEntry* k : kernels_for(dtype, L))
-        if (k->nparts == 1 && max_radix(k) <= 16) ks.push_back(k);
+        if (!k->extra && k->nparts == 1 && max_radix(k) <= 16) ks.push_back(k);
     if (ks.empty()) return nullptr;
     if (!strided) return ks[0];
     for (const KernelEntry* k : ks)
@@ -259,6 +272,70 @@ static const KernelEntry* default_kernel(int dtype, int L, bool strided) {
     for (const KernelEntry* k : ks)
         if (k->nparts == 1) return k;
     return ks[0];
+}
+
+// ---- measured default kernels ---------------------------------------------
+// kernel_defaults.txt: per precision, line kind and length one spec per class
+// of grid bytes.
+namespace {
+enum LineKind { kContiguous = 0, kStrided = 1, kTransposing = 2 };
+struct KernelDefault {
+    int dtype;
+    int kind;              // LineKind
+    int L;
+    const char* spec[3];
+};
+const KernelDefault kKernelDefaults[] = {
+#include "_gen/kernel_defaults.inc"
+};
+}  // namespace
+
+struct AxisSpec {
+    bool given = false;
+    std::vector<int> rad;
+    long W = 0, tpl = 0, P = 1;
+    int xcd = 0;
+    int io = kIoAuto;
+};
+static bool parse_axis_spec(const std::string& val, AxisSpec* sp);
+static const KernelEntry* find_kernel(int dtype, int L, const AxisSpec& sp);
+
+// Passes of fewer lines than the device has CUs keep the radix-sequence rules'
+// kernels (fewest stages): they are one latency chain whatever the tile
+// (8 x 8 x 512 complex128: 12.4 to 13.7 us a transform with either).
+constexpr int64_t kTableMinLines = 256;
+// Size classes of kernel_defaults.txt.  The first line lies between the 4 MiB
+// and the 16 MiB timings: at 4 MiB the large grids' kernels of 128-point lines
+// (complex128) move 1.5 TB/s on strided lines where the narrow tiles move
+// 2.0, at 64 MiB 3.9 against 3.6.  The second: over boxes of 12 shapes the
+// second class's plans took 0.91, 0.96, 0.94 and 1.06 of the third's time at
+// 160, 208, 256 and 330 MiB of complex128, 0.93, 0.99, 1.00 and 1.26 of
+// complex64.
+constexpr int64_t kSmallGridBytes = int64_t(8) << 20;
+static int64_t large_grid_bytes(int dtype) { return int64_t(dtype == OFFT_C2C_F64 ? 256 : 192) << 20; }
+
+// The measured default kernel and tile width of a pass over `lines` lines of
+// length L in a batch of grids of `bytes`; null where the table has none.
+static const KernelEntry* table_kernel(int dtype, int L, LineKind kind, int64_t lines, int64_t bytes, int* logW) {
+    if (lines < kTableMinLines) return nullptr;
+    const int cls = bytes <= kSmallGridBytes ? 0 : (bytes <= large_grid_bytes(dtype) ? 1 : 2);
+    for (const KernelDefault& d : kKernelDefaults) {
+        if (d.dtype != dtype || d.kind != kind || d.L != L) continue;
+        AxisSpec sp;
+        const KernelEntry* k = parse_axis_spec(d.spec[cls], &sp) ? find_kernel(dtype, L, sp) : nullptr;
+        if (k) *logW = fit_logW(k, ilog2(sp.W), dtype, kind == kTransposing ? kGeomTranspose : kGeomNatural);
+        return k;
+    }
+    return nullptr;
+}
+
+// The kernel and width of a pass that does not transpose: the table's, or
+// the rules' where it has none.
+static const KernelEntry* pass_kernel(int dtype, int L, bool strided, int64_t lines, int64_t bytes, int* logW) {
+    if (const KernelEntry* k = table_kernel(dtype, L, strided ? kStrided : kContiguous, lines, bytes, logW)) return k;
+    const KernelEntry* k = default_kernel(dtype, L, strided);
+    *logW = default_logW(k, dtype, strided);
+    return k;
 }
 
 static bool axis_strided(int axis, const int64_t dims[3]) {
@@ -298,31 +375,36 @@ static bool streamed_long_stride(int dtype, const int64_t* dims, int ndim, int a
 static const KernelEntry* default_kernel_transpose(int dtype, int L) {
     if (L >= 512)
         for (const KernelEntry* k : kernels_for(dtype, L))
-            if (k->nparts == 2 && k->launch_t && max_radix(k) <= 16 && tile_fits_transpose(k, 4, dtype)) return k;
+            if (!k->extra && k->nparts == 2 && k->launch_t && max_radix(k) <= 16 && tile_fits_transpose(k, 4, dtype)) return k;
     for (const KernelEntry* k : kernels_for(dtype, L))
-        if (k->nparts == 1 && k->launch_t && max_radix(k) <= 16) return k;
+        if (!k->extra && k->nparts == 1 && k->launch_t && max_radix(k) <= 16) return k;
     for (const KernelEntry* k : kernels_for(dtype, L))
-        if (k->nparts == 1 && k->launch_t) return k;
+        if (!k->extra && k->nparts == 1 && k->launch_t) return k;
     return nullptr;
 }
 
 // The heuristic kernel and width of every axis, for the geometry the
 // choice's order and output order give it.
-static void assign_default_kernels(PlanChoice& c, int dtype, const int64_t dims[3]) {
+static void assign_default_kernels(PlanChoice& c, int dtype, const int64_t dims[3], int64_t batch,
+                                   bool rules_only = false) {
+    const int64_t points = dims[0] * dims[1] * dims[2] * batch;
     for (int ax = 0; ax < 3; ++ax) {
         c.k[ax] = nullptr;
         c.logW[ax] = 0;
         if (dims[ax] <= 1) continue;
         const int g = axis_geom(c, ax);
         const KernelEntry* k;
-        int logW;
+        int logW = 0;
         if (g == kGeomTranspose) {
-            k = default_kernel_transpose(dtype, (int)dims[ax]);
-            logW = k ? fit_logW(k, 4, dtype, g) : 0;
+            k = table_kernel(dtype, (int)dims[ax], kTransposing, points / dims[ax], points * (int64_t)elem_size(dtype), &logW);
+            if (!k) {
+                k = default_kernel_transpose(dtype, (int)dims[ax]);
+                logW = k ? fit_logW(k, 4, dtype, g) : 0;
+            }
         } else {
             const bool strided = make_pass(dims, 1, ax, g, nullptr, 0).M2 > 1;
-            k = default_kernel(dtype, (int)dims[ax], strided);
-            logW = default_logW(k, dtype, strided);
+            k = pass_kernel(dtype, (int)dims[ax], strided, rules_only ? 0 : points / dims[ax],
+                            points * (int64_t)elem_size(dtype), &logW);
         }
         if (k) {
             c.k[ax] = k;
@@ -344,17 +426,16 @@ PassPlan contiguous_pass(int dtype, int L, int64_t lines, int64_t grid_bytes) {
     p.mode = 0;
     p.xcd = 0;
     p.tw = nullptr;
-    p.k = default_kernel(dtype, L, false);
-    p.logW = default_logW(p.k, dtype, false);
+    p.k = pass_kernel(dtype, L, false, lines, grid_bytes, &p.logW);
     p.stream = resolve_stream(kIoAuto, grid_bytes);
     return p;
 }
 
-PlanChoice default_choice(int dtype, const int64_t dims[3]) {
+PlanChoice default_choice(int dtype, const int64_t dims[3], int64_t batch, bool rules_only) {
     PlanChoice c;
     c.order[0] = 2; c.order[1] = 1; c.order[2] = 0;   // c, then b, then a
     c.tax = -1;
-    assign_default_kernels(c, dtype, dims);
+    assign_default_kernels(c, dtype, dims, batch, rules_only);
     return c;
 }
 
@@ -362,12 +443,12 @@ PlanChoice default_choice(int dtype, const int64_t dims[3]) {
 // abc lines in, cba rows out), so the first pass reads contiguous lines and
 // only pass b runs on strided lines of one buffer; without an axis a, the
 // pass along c transposes (abc rows in, strided cba lines out).
-PlanChoice default_choice_reversed(int dtype, const int64_t dims[3]) {
-    if (!reversal_moves_data(dims)) return default_choice(dtype, dims);
+PlanChoice default_choice_reversed(int dtype, const int64_t dims[3], int64_t batch) {
+    if (!reversal_moves_data(dims)) return default_choice(dtype, dims, batch);
     PlanChoice c;
     c.order[0] = 2; c.order[1] = 1; c.order[2] = 0;
     c.tax = dims[0] > 1 ? 0 : 2;
-    assign_default_kernels(c, dtype, dims);
+    assign_default_kernels(c, dtype, dims, batch);
     return c;
 }
 
@@ -383,7 +464,7 @@ std::vector<PlanChoice> candidate_choices(int dtype, const int64_t dims[3]) {
         const bool strided = axis_strided(ax, dims);
         std::vector<const KernelEntry*> ks = kernels_for(dtype, (int)dims[ax]);
         for (const KernelEntry* k : ks) {
-            if (k->nparts > 1 && !strided) continue;
+            if ((k->nparts > 1 && !strided) || k->extra) continue;
             const int l0 = default_logW(k, dtype, strided);
             for (int dl = -1; dl <= 1; ++dl) {
                 const int lw = l0 + dl;
@@ -435,16 +516,6 @@ static void axis_to_string(std::ostringstream& os, const KernelEntry* k, int log
     if (io == kIoStream) os << "/s";
     if (io == kIoCached) os << "/c";
 }
-
-namespace {
-struct AxisSpec {
-    bool given = false;
-    std::vector<int> rad;
-    long W = 0, tpl = 0, P = 1;
-    int xcd = 0;
-    int io = kIoAuto;
-};
-}  // namespace
 
 static bool parse_axis_spec(const std::string& val, AxisSpec* sp) {
     sp->given = true;
@@ -617,7 +688,7 @@ bool choice_from_string(const char* s, int dtype, const int64_t dims[3], PlanCho
     if (c.tax >= 0 && (!reversal_moves_data(dims) || dims[c.tax] <= 1)) return false;
     if (!slab_fits(c, dims) || !col_fits(c, dims, false)) return false;
     // axes the string leaves out take the heuristic's kernel for their geometry
-    assign_default_kernels(c, dtype, dims);
+    assign_default_kernels(c, dtype, dims, 1);
     for (int ax = 0; ax < 3; ++ax) {
         if (!spec[ax].given) continue;
         const AxisSpec& sp = spec[ax];
@@ -666,19 +737,23 @@ PassPlan make_pass_nd(int ndim, const int64_t* dims, int64_t batch, int ax, cons
 // Heuristic: passes from the last (contiguous) axis to the first, each axis
 // with the kernel and width the three-dimensional heuristic gives a line of
 // its length and stride kind.
-NdChoice default_choice_nd(int dtype, int ndim, const int64_t* dims) {
+NdChoice default_choice_nd(int dtype, int ndim, const int64_t* dims, int64_t batch) {
     NdChoice c;
     c.ndim = ndim;
     for (int i = 0; i < ndim; ++i) c.order[i] = ndim - 1 - i;
+    int64_t points = batch;
+    for (int i = 0; i < ndim; ++i) points *= dims[i];
     for (int ax = 0; ax < ndim; ++ax) {
         c.k[ax] = nullptr;
         c.logW[ax] = 0;
         if (dims[ax] <= 1) continue;
         const bool strided = make_pass_nd(ndim, dims, 1, ax, nullptr, 0).M2 > 1;
-        const KernelEntry* k = default_kernel(dtype, (int)dims[ax], strided);
+        int logW = 0;
+        const KernelEntry* k = pass_kernel(dtype, (int)dims[ax], strided, points / dims[ax],
+                                           points * (int64_t)elem_size(dtype), &logW);
         if (k) {
             c.k[ax] = k;
-            c.logW[ax] = default_logW(k, dtype, strided);
+            c.logW[ax] = logW;
             c.xcd[ax] = default_xcd(kGeomNatural, strided, streamed_long_stride(dtype, dims, ndim, ax));
         }
     }

@@ -74,6 +74,18 @@ void plan_features(int dtype, const int64_t dims[3], int64_t batch, const PlanCh
                 case 2: g[5] += 1.f; break;
                 case 3: g[6] += 1.f; break;
                 case 5: g[7] += 1.f; break;
+                // composite radices count as their inner ones
+                case 6: g[5] += 1.f; g[6] += 1.f; break;
+                case 9: g[6] += 2.f; break;
+                case 10: g[5] += 1.f; g[7] += 1.f; break;
+                case 12: g[4] += 1.f; g[6] += 1.f; break;
+                case 15: g[6] += 1.f; g[7] += 1.f; break;
+                case 18: g[5] += 1.f; g[6] += 2.f; break;
+                case 20: g[4] += 1.f; g[7] += 1.f; break;
+                case 24: g[3] += 1.f; g[6] += 1.f; break;
+                case 25: g[7] += 2.f; break;
+                case 27: g[6] += 3.f; break;
+                case 30: g[5] += 1.f; g[6] += 1.f; g[7] += 1.f; break;
                 default: break;
             }
         }

@@ -210,7 +210,8 @@ static int exhaustive_dims(offt_plan_s* p, const offt_opts& o, const int64_t dim
                            const TuneBuffers& B, PlanChoice* choice, float* win_ms_out, int* timed) {
     hipStream_t s = static_cast<hipStream_t>(o.stream);
     const bool rev = reversed && reversal_moves_data(dims);
-    const PlanChoice heur = rev ? default_choice_reversed(p->dtype, dims) : default_choice(p->dtype, dims);
+    const PlanChoice heur = rev ? default_choice_reversed(p->dtype, dims, p->batch)
+                                : default_choice(p->dtype, dims, p->batch, p->rules_only);
     std::vector<int> taxes;   // transposing axes to try
     if (rev) {
         for (int t : {0, 2})
@@ -259,6 +260,7 @@ static int exhaustive_dims(offt_plan_s* p, const offt_opts& o, const int64_t dim
                 // kernels whose LDS exchanges run in parts serve strided lines
                 // (and transposing passes, whose one side is strided)
                 if (k->nparts > 1 && shape.M2 == 1) continue;
+                if (p->rules_only && k->extra) continue;
                 if (g == kGeomTranspose && !k->launch_t) continue;
                 const int top = fit_logW(k, 10, p->dtype, g);
                 // widths below 1/16 of the widest that fits are never competitive;
@@ -591,7 +593,7 @@ static int exhaustive_nd(offt_plan_s* p, const offt_opts& o, NdChoice* choice, f
     }
     const int D = p->ndim;
     const int64_t* dims = p->nd_dims;
-    NdChoice best = default_choice_nd(p->dtype, D, dims);
+    NdChoice best = default_choice_nd(p->dtype, D, dims, p->batch);
     // runner-up (kernel, width) per axis, tried with the winning order at the end
     const KernelEntry* second_k[kMaxDims] = {};
     int second_lw[kMaxDims] = {};
@@ -676,7 +678,7 @@ static int exhaustive_nd(offt_plan_s* p, const offt_opts& o, NdChoice* choice, f
         if (perm != axes) orders.push_back(perm);
     } while (std::next_permutation(perm.begin(), perm.end()));
     // the heuristic plan itself first, then every order with the fastest kernels
-    NdChoice winner = default_choice_nd(p->dtype, D, dims);
+    NdChoice winner = default_choice_nd(p->dtype, D, dims, p->batch);
     float wms = 1e30f;
     if (rc == OFFT_SUCCESS) {
         PassPlan passes[kMaxDims];
