@@ -68,6 +68,7 @@ int attach_twiddles(offt_plan_s* p, PassPlan* passes, int npass, hipStream_t s) 
 int set_choice(offt_plan_s* p, const PlanChoice& c, hipStream_t s) {
     p->choice = c;
     p->npass = build_passes(c, p->dims, p->batch, p->passes);
+    if (p->allow_fuse) set_fuse(p->passes, p->npass);
     for (int i = 0; i < p->npass; ++i)
         if (!p->passes[i].k) return OFFT_ERR_UNSUPPORTED_SIZE;
     return attach_twiddles(p, p->passes, p->npass, s);
@@ -85,6 +86,7 @@ int set_choice_b(offt_plan_s* p, const PlanChoice& c, hipStream_t s) {
     p->choice_b = c;
     const int n = build_passes(c, rd, p->batch, p->passes_b);
     if (n != p->npass) return OFFT_ERR_BAD_PLAN;
+    if (p->allow_fuse) set_fuse(p->passes_b, n);
     for (int i = 0; i < n; ++i)
         if (!p->passes_b[i].k) return OFFT_ERR_UNSUPPORTED_SIZE;
     return attach_twiddles(p, p->passes_b, n, s);
@@ -127,6 +129,21 @@ int exec_passes(const offt_plan_s* p, const PassPlan* passes, int npass, const v
     // column block) before the next
     const int first_slab = slab_start(passes, npass);
     for (int i = i0; i < std::min(i1, first_slab); ++i) {
+        const int f = passes[i].fuse;
+        if (f > 1 && i + f <= i1) {
+            // a block kernel: reads what pass i reads, writes what the last of its passes writes
+            const bool last = i + f == npass;
+            const void *src = nullptr, *src_f = nullptr;
+            void *dst = nullptr, *dst_f = nullptr;
+            if (!pass_io(passes, npass, i, in, out, work, &src, &dst) ||
+                !pass_io(passes, npass, i + f - 1, in, out, work, &src_f, &dst_f))
+                return OFFT_ERR_BAD_PLAN;
+            if (launch_block(passes + i, src, dst_f, bwd && i == 0, bwd && last,
+                             (bwd && last && norm) ? 1.0 / (double)N : 1.0, s) != hipSuccess)
+                return OFFT_ERR_HIP;
+            i += f - 1;
+            continue;
+        }
         const int rc = launch(i, passes[i], 0);
         if (rc != OFFT_SUCCESS) return rc;
     }
@@ -279,6 +296,7 @@ offt_plan_t offt_plan_ex(int64_t Na, int64_t Nb, int64_t Nc, int dtype, int64_t 
     p->batch = batch;
     p->normalize = opts.normalize_inverse ? 1 : 0;
     p->layout = opts.layout;
+    p->allow_fuse = opts.tune != OFFT_TUNE_FORCED;
     hipStream_t s = static_cast<hipStream_t>(opts.stream);
 
     PlanChoice choice = reversed ? default_choice_reversed(dtype, dims, batch) : default_choice(dtype, dims, batch);
@@ -365,6 +383,7 @@ offt_plan_t offt_plan_nd(int ndim, const int64_t* dims, int dtype, int64_t batch
     for (int i = 0; i < ndim; ++i) p->nd_dims[i] = dims[i];
     p->batch = batch;
     p->normalize = opts.normalize_inverse ? 1 : 0;
+    p->allow_fuse = opts.tune != OFFT_TUNE_FORCED;
     hipStream_t s = static_cast<hipStream_t>(opts.stream);
     if (opts.tune == OFFT_TUNE_EXHAUSTIVE || opts.tune == OFFT_TUNE_LEARNED) {
         rc = select_plan_nd(p, opts, &choice);
@@ -372,6 +391,7 @@ offt_plan_t offt_plan_nd(int ndim, const int64_t* dims, int dtype, int64_t batch
     }
     p->ndc = choice;
     p->npass = build_passes_nd(choice, p->nd_dims, batch, p->passes);
+    if (p->allow_fuse) set_fuse(p->passes, p->npass);
     for (int i = 0; i < p->npass && rc == OFFT_SUCCESS; ++i)
         if (!p->passes[i].k) rc = OFFT_ERR_UNSUPPORTED_SIZE;
     if (rc == OFFT_SUCCESS) rc = attach_twiddles(p, p->passes, p->npass, s);

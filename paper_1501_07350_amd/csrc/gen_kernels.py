@@ -18,6 +18,8 @@ instantiations and a table; <outdir>/registry_parts.inc lists the tables and
 from __future__ import annotations
 
 import functools
+import itertools
+import math
 import os
 import sys
 
@@ -185,7 +187,12 @@ def entries(prec="f64", parts=True):
                     if splits(L, seq, P):
                         for t in tpls:
                             out.append((L, seq, t, P))
-        # the measured defaults, where the sequences above do not hold them
+        # the block kernels' sequences (their stand-alone passes) and the
+        # measured defaults, where the sequences above do not hold them
+        if L <= BLOCK_MAX_L and block_seq(L):
+            e = (L, block_seq(L), L // max(block_seq(L)), 1)
+            if e not in out:
+                out.append(e)
         for seq, t, P in default_entries(prec, L):
             if (parts or P == 1) and (L, seq, t, P) not in out:
                 out.append((L, seq, t, P))
@@ -200,6 +207,107 @@ def legacy(prec, L, seq, tpl, P):
     return seq in radix_seqs(L) and tpl in tpls and (P == 1 or (L >= PARTS_MIN_L and P in (2, 4) and splits(L, seq, P)))
 
 
+# Longest line of a block kernel (fft_block.hpp).
+BLOCK_MAX_L = 256
+# A precision has two block kernels.  Lines of up to 100 points have radices up
+# to 10 and fit 80 registers in binary32 (six waves per SIMD) and 128 in
+# binary64; the longer lines' radices 12 to 16 take up to 128, and in binary64
+# more than 1024 threads leave.  (kernel, longest line, threads, attribute)
+BLOCK_KERNELS = {"f64": (("short", 100, 1024, ""), ("long", BLOCK_MAX_L, 512, "")),
+                 "f32": (("short", 100, 1024, "__attribute__((amdgpu_waves_per_eu(6))) "), ("long", BLOCK_MAX_L, 1024, ""))}
+# Radices of the block kernels' stages.
+BLOCK_RADICES = (2, 3, 4, 5, 6, 8, 9, 10, 12, 15, 16)
+
+
+@functools.lru_cache(maxsize=None)
+def block_seq(L):
+    """Radix sequence of a block kernel's lines: the fewest stages, of those
+    the most even radices (one butterfly per thread in every stage, so uneven
+    ones leave threads idle), largest first; None if the radices do not
+    reach L in three stages."""
+    best = None
+    for n in (1, 2, 3):
+        for seq in itertools.combinations_with_replacement(BLOCK_RADICES, n):
+            if math.prod(seq) == L and (n > 1 or L <= 10):
+                key = seq[-1] / seq[0]
+                if best is None or key < best[0]:
+                    best = (key, sorted(seq, reverse=True))
+        if best:
+            return best[1]
+    return None
+
+
+def block_cases(prec):
+    """Kernel cases (L, radix sequence, threads per line) of the block kernel:
+    one per length up to BLOCK_MAX_L, one butterfly per thread in every
+    stage."""
+    return [(L, block_seq(L), L // min(block_seq(L))) for L in lengths() if L <= BLOCK_MAX_L and block_seq(L)]
+
+
+def emit_block(outdir):
+    """block_<kernel>_<prec>.hip (the block kernels of a precision, a switch
+    over their cases per axis) and block_cases.inc (the cases for the
+    planner)."""
+    files, inc = [], []
+    for prec, vt, dcode in (("f64", "double2", 0), ("f32", "float2", 1)):
+        cases = block_cases(prec)
+        for name, max_l, threads, attr in BLOCK_KERNELS[prec]:
+            lines = ["// generated by gen_kernels.py -- do not edit",
+                     '#include "offt_internal.h"',
+                     '#include "fft_block.hpp"',
+                     "namespace offt {",
+                     "namespace {",
+                     "struct Rows {",
+                     f"    __device__ __forceinline__ void operator()(const BlockArgs& a, {vt}* lds, const {vt}* tw, int tid) const {{",
+                     "        switch (a.kid[0]) {"]
+            used = [(i, c) for i, c in enumerate(cases) if c[0] <= max_l]
+            for i, (L, seq, tpl) in used:
+                lines.append(f"            case {i}: block_rows<{vt}, {L}, {tpl}, {', '.join(map(str, seq))}>(a, lds, tw, tid); break;")
+            lines += ["            default: break;", "        }", "    }", "};", "struct Columns {",
+                      f"    __device__ __forceinline__ void operator()(const BlockArgs& a, {vt}* lds, const {vt}* tw, {vt}* go, "
+                      "int axis, int tid) const {",
+                      "        switch (axis == 1 ? a.kid[1] : a.kid[2]) {"]
+            for i, (L, seq, tpl) in used:
+                lines.append(f"            case {i}: block_columns<{vt}, {L}, {tpl}, {', '.join(map(str, seq))}>(a, lds, tw, go, axis, tid); break;")
+            lines += ["            default: break;", "        }", "    }", "};",
+                      f"__global__ void __launch_bounds__({threads}) {attr}fft_block_{name}_{prec}(BlockArgs a) {{",
+                      "    extern __shared__ __align__(16) unsigned char smem_raw[];",
+                      f"    block_body<{vt}>(a, reinterpret_cast<{vt}*>(smem_raw), (int64_t)blockIdx.x, Rows{{}}, Columns{{}});",
+                      "}",
+                      "}  // namespace",
+                      f"hipError_t launch_block_{name}_{prec}(const BlockArgs& a, int64_t nblocks, int threads, size_t lds, "
+                      "hipStream_t s) {",
+                      "    static std::atomic<size_t> lds_set{65536};",
+                      f"    return launch_block_kernel(&fft_block_{name}_{prec}, lds_set, a, nblocks, threads, lds, s);",
+                      "}",
+                      "}  // namespace offt"]
+            path = os.path.join(outdir, f"block_{name}_{prec}.hip")
+            _write(path, "\n".join(lines) + "\n")
+            files.append(path)
+        for L, seq, tpl in cases:
+            padded = ", ".join(str(x) for x in (list(seq) + [0] * (8 - len(seq))))
+            inc.append(f"    {{{dcode}, {L}, {len(seq)}, {{{padded}}}, {tpl}}},")
+    _write(os.path.join(outdir, "block_cases.inc"), "\n".join(inc) + "\n")
+    protos = []
+    for prec in BLOCK_KERNELS:
+        for name, *_ in BLOCK_KERNELS[prec]:
+            protos.append(f"hipError_t launch_block_{name}_{prec}(const BlockArgs& a, int64_t nblocks, int threads, size_t lds, hipStream_t s);")
+    protos.append("struct BlockKernel { int dtype; int max_l; int threads; hipError_t (*launch)(const BlockArgs&, int64_t, int, size_t, hipStream_t); };")
+    protos.append("static const BlockKernel kBlockKernels[] = {")
+    for prec, dcode in (("f64", 0), ("f32", 1)):
+        for name, max_l, threads, _ in BLOCK_KERNELS[prec]:
+            protos.append(f"    {{{dcode}, {max_l}, {threads}, &launch_block_{name}_{prec}}},")
+    protos.append("};")
+    _write(os.path.join(outdir, "block_kernels.inc"), "\n".join(protos) + "\n")
+    return files
+
+
+def _write(path, text):
+    if not os.path.exists(path) or open(path).read() != text:
+        with open(path, "w") as f:
+            f.write(text)
+
+
 def emit_defaults(outdir):
     """kernel_defaults.inc: {dtype, line kind, L, {spec per size class}} rows."""
     rows = []
@@ -211,10 +319,7 @@ def emit_defaults(outdir):
         rows.append(f"    {{{0 if prec == 'f64' else 1}, {'cst'.index(kind)}, {L}, "
                     f"{{{', '.join(chr(34) + s + chr(34) for s in specs)}}}}},")
     text = "\n".join(rows) + "\n"
-    path = os.path.join(outdir, "kernel_defaults.inc")
-    if not os.path.exists(path) or open(path).read() != text:
-        with open(path, "w") as f:
-            f.write(text)
+    _write(os.path.join(outdir, "kernel_defaults.inc"), text)
 
 
 def emit(outdir):
@@ -223,8 +328,7 @@ def emit(outdir):
     tables = []
     for prec, vt, dcode in (("f64", "double2", 0), ("f32", "float2", 1)):
         ents = entries(prec)
-        extras = [(L, seq, t, P) for L in lengths() for seq, t, P in default_entries(prec, L)
-                  if not legacy(prec, L, seq, t, P)]
+        extras = [e for e in ents if not legacy(prec, *e)]
         for part in range(PARTS):
             mine = ents[part::PARTS]
             name = f"kernels_{prec}_{part}"
@@ -279,10 +383,7 @@ def emit(outdir):
             lines.append(f"const int g_{name}_n = {len(mine)};")
             lines.append("}  // namespace offt")
             path = os.path.join(outdir, name + ".hip")
-            text = "\n".join(lines) + "\n"
-            if not os.path.exists(path) or open(path).read() != text:
-                with open(path, "w") as f:
-                    f.write(text)
+            _write(path, "\n".join(lines) + "\n")
             tables.append(name)
     inc = []
     for t in tables:
@@ -290,11 +391,8 @@ def emit(outdir):
     inc.append("#define OFFT_REGISTRY_TABLES \\")
     inc.append(" \\\n".join(f"    {{g_{t}, g_{t}_n}}," for t in tables))
     text = "\n".join(inc) + "\n"
-    path = os.path.join(outdir, "registry_parts.inc")
-    if not os.path.exists(path) or open(path).read() != text:
-        with open(path, "w") as f:
-            f.write(text)
-    return [os.path.join(outdir, t + ".hip") for t in tables]
+    _write(os.path.join(outdir, "registry_parts.inc"), text)
+    return [os.path.join(outdir, t + ".hip") for t in tables] + emit_block(outdir)
 
 
 if __name__ == "__main__":

@@ -68,6 +68,7 @@ int offt_exec_noalloc(int64_t Na, int64_t Nb, int64_t Nc, int dtype, int64_t bat
     // the heuristic plan of offt_plan (host-side choice, nothing allocated)
     PassPlan passes[3];
     const int npass = build_passes(default_choice(dtype, dims, batch), dims, batch, passes);
+    set_fuse(passes, npass);
     for (int i = 0; i < npass; ++i)
         if (!passes[i].k) { set_error(OFFT_ERR_UNSUPPORTED_SIZE); return OFFT_ERR_UNSUPPORTED_SIZE; }
     // one table per distinct length in the scratch array, written before the

@@ -4,9 +4,11 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <atomic>
 #include <string>
 #include <vector>
 
+#include "fft_block.hpp"
 #include "fft_device.hpp"
 
 namespace offt {
@@ -84,12 +86,42 @@ struct PassPlan {
     // next block.  0: the whole grid at once.
     int64_t col = 0;
     int64_t ncol = 0;
+    // block kernel (fft_block.hpp): this pass and the next fuse - 1 run as one
+    // launch over blocks of `fuse` axes when a call covers them all; 0: alone
+    int fuse = 0;
     // a strided pass restricted to one column block (PassArgs): lines per
     // m1 (0: M2), log2 of the block width (-1: none), row length, first column
     int64_t lpm = 0;
     int blk_logw = -1;
     int64_t blk_ld = 0, blk_off = 0;
 };
+
+// One axis of a block kernel (generated table): radix sequence and threads
+// per line of the lines of length L.
+struct BlockCase {
+    int dtype;
+    int L;
+    int nstages;
+    int radices[kMaxStages];
+    int tpl;
+};
+// Marks the passes of a list that run as block kernels (PassPlan::fuse).
+void set_fuse(PassPlan* ps, int n);
+// Launches passes ps[0..ps[0].fuse) as one block kernel.
+hipError_t launch_block(const PassPlan* ps, const void* in, void* out, int conj_in, int conj_out, double scale,
+                        hipStream_t s);
+template <typename K>
+hipError_t launch_block_kernel(K* k, std::atomic<size_t>& lds_set, const BlockArgs& a, int64_t nblocks, int threads,
+                               size_t lds, hipStream_t s) {
+    // lds_set: the kernel's dynamic LDS limit so far (64 KiB until raised)
+    if (lds > lds_set.load()) {
+        const hipError_t e = hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+        lds_set.store(lds);
+    }
+    hipLaunchKernelGGL(k, dim3((unsigned)nblocks), dim3(threads), lds, s, a);
+    return hipGetLastError();
+}
 
 // Pass p restricted to planes [p0, p0 + np) of a slab schedule; *elem_off
 // receives the element offset of plane p0.

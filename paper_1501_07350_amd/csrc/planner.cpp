@@ -415,6 +415,27 @@ static void assign_default_kernels(PlanChoice& c, int dtype, const int64_t dims[
     }
 }
 
+static int fuse_rule(int dtype, int64_t A, int64_t B, int64_t C, int64_t grids);
+static const KernelEntry* block_kernel_entry(int dtype, int64_t L);
+
+// The last axes of a default plan that run as a block kernel take kernels of
+// its radix sequences, so that the passes one by one give the same bits.
+// (first: index of dims[0] in k and logW.)
+static void assign_block_kernels(int dtype, int ndim, const int64_t* dims, int64_t batch, const KernelEntry** k,
+                                 int* logW, int first = 0) {
+    int64_t grids = batch;
+    for (int i = 0; i < ndim - 3; ++i) grids *= dims[i];
+    const int64_t A = ndim >= 3 ? dims[ndim - 3] : 1;
+    const int f = fuse_rule(dtype, A, dims[ndim - 2], dims[ndim - 1], grids);
+    for (int i = 0; i < f; ++i) {
+        const int ax = ndim - 1 - i;
+        const KernelEntry* e = block_kernel_entry(dtype, dims[ax]);
+        if (!e) continue;
+        k[first + ax] = e;
+        logW[first + ax] = default_logW(e, dtype, i > 0);
+    }
+}
+
 PassPlan contiguous_pass(int dtype, int L, int64_t lines, int64_t grid_bytes) {
     PassPlan p;
     p.axis = 2;
@@ -436,6 +457,7 @@ PlanChoice default_choice(int dtype, const int64_t dims[3], int64_t batch, bool 
     c.order[0] = 2; c.order[1] = 1; c.order[2] = 0;   // c, then b, then a
     c.tax = -1;
     assign_default_kernels(c, dtype, dims, batch, rules_only);
+    if (!rules_only) assign_block_kernels(dtype, 3, dims, batch, c.k, c.logW);
     return c;
 }
 
@@ -449,6 +471,8 @@ PlanChoice default_choice_reversed(int dtype, const int64_t dims[3], int64_t bat
     c.order[0] = 2; c.order[1] = 1; c.order[2] = 0;
     c.tax = dims[0] > 1 ? 0 : 2;
     assign_default_kernels(c, dtype, dims, batch);
+    // the passes over c and b come before the transposing one over a
+    if (c.tax == 0) assign_block_kernels(dtype, 2, dims + 1, batch * dims[0], c.k, c.logW, 1);
     return c;
 }
 
@@ -757,6 +781,7 @@ NdChoice default_choice_nd(int dtype, int ndim, const int64_t* dims, int64_t bat
             c.xcd[ax] = default_xcd(kGeomNatural, strided, streamed_long_stride(dtype, dims, ndim, ax));
         }
     }
+    assign_block_kernels(dtype, ndim, dims, batch, c.k, c.logW);
     return c;
 }
 
@@ -877,6 +902,136 @@ int build_passes(const PlanChoice& c, const int64_t dims[3], int64_t batch, Pass
         }
     }
     return n;
+}
+
+// ---- block kernels --------------------------------------------------------------
+
+// The block kernels of each precision (generated table): longest line and
+// most threads, the kernel of the shorter lines first.
+#include "_gen/block_kernels.inc"
+static const BlockCase kBlockCases[] = {
+#include "_gen/block_cases.inc"
+};
+
+// Case of the block kernel for lines of kernel k's radix sequence, or -1 (the
+// index counts the cases of k's precision).
+static int block_case(const KernelEntry* k) {
+    int i = 0;
+    for (const BlockCase& c : kBlockCases) {
+        if (c.dtype != k->dtype) continue;
+        if (c.L == k->L && c.nstages == k->nstages && std::equal(c.radices, c.radices + c.nstages, k->radices)) return i;
+        ++i;
+    }
+    return -1;
+}
+
+static const BlockCase* block_case_of_length(int dtype, int64_t L) {
+    for (const BlockCase& c : kBlockCases)
+        if (c.dtype == dtype && c.L == L) return &c;
+    return nullptr;
+}
+
+static const KernelEntry* block_kernel_entry(int dtype, int64_t L) {
+    if (L < 2 || L > OFFT_MAX_AXIS) return nullptr;
+    for (const KernelEntry* k : kernels_for(dtype, (int)L))
+        if (k->nparts == 1 && block_case(k) >= 0) return k;
+    return nullptr;
+}
+
+// Axes that run as one block kernel, by size: 3 (blocks are whole A x B x C
+// grids), 2 (B x C planes) or 0 (each pass alone).  What decides is whether a
+// CU holds two blocks (one block's loads and stores then overlap the other's
+// stages) and whether there are blocks for enough CUs.  Measured on MI355X,
+// separate passes against the block kernel, per transform:
+//   whole grids    16^3 complex128 14.6 -> 9.5 us, 1024 of them 65 -> 38 us;
+//                  18^3 alone 13.1 -> 13.4 us (planes: 10.3), 1024 93 -> 70 us
+//   planes         64^3 complex64 14.8 -> 11.8 us, 64 of them 118 -> 102 us;
+//                  64 x 32^3 complex128 37.7 -> 29.5 us
+//   one block per  8 x 100^3 complex64 65.8 -> 75.4 us (in the Infinity Cache),
+//   CU             64 of them 617 -> 549 us, 128^4 2.97 -> 2.80 ms (streaming);
+//                  128^3 alone 35.6 -> 27.3 us, 8 of them equal
+//   few blocks     12 x 150 x 60 complex64 14.3 -> 16.4 us
+static int fuse_rule(int dtype, int64_t A, int64_t B, int64_t C, int64_t grids) {
+    if (C < 2 || B < 2 || !block_case_of_length(dtype, B) || !block_case_of_length(dtype, C)) return 0;
+    const int64_t es = (int64_t)elem_size(dtype);
+    constexpr int64_t kTwoPerCu = 80 * 1024;
+    const int64_t planes = A * grids;
+    // up to 64 rows the contiguous pass keeps the rules' kernels, radix 16 in
+    // complex128 and up to 8 in complex64
+    if (planes * B <= 64) return 0;
+    if (A > 1 && block_case_of_length(dtype, A)) {
+        const int64_t lds = block_lds_elems((int)A, (int)B, (int)C) * es;
+        if (lds <= lds_limit() && (grids >= 512 || (lds <= kTwoPerCu && A * B * C <= 4096))) return 3;
+    }
+    const int64_t lds = block_lds_elems(1, (int)B, (int)C) * es;
+    if (lds > lds_limit()) return 0;
+    if (lds <= kTwoPerCu ? (B * C <= 4096 || planes >= 64)
+                         : ((planes >= 64 && planes <= 256) || planes * B * C * es > kStreamMinBytes))
+        return 2;
+    return 0;
+}
+
+void set_fuse(PassPlan* ps, int n) {
+    for (int i = 0; i + 1 < n; ++i) {
+        const PassPlan &c = ps[i], &b = ps[i + 1];
+        // rows, then the lines across them, of one contiguous block
+        if (c.mode != 0 || b.mode != 1 || b.M2 != c.L || c.M1 != b.M1 * b.L || c.slab || c.col || b.slab || b.col)
+            continue;
+        if (!c.k || !b.k || block_case(c.k) < 0 || block_case(b.k) < 0) continue;
+        const PassPlan* a = i + 2 < n ? &ps[i + 2] : nullptr;
+        const bool whole = a && a->mode == 1 && !a->slab && !a->col && a->k && a->M2 == b.M2 * b.L &&
+                           b.M1 == a->M1 * a->L && block_case(a->k) >= 0;
+        const int f = fuse_rule(c.k->dtype, whole ? a->L : 1, b.L, c.L, whole ? a->M1 : b.M1);
+        if (f > 1) ps[i].fuse = f;
+    }
+}
+
+hipError_t launch_block(const PassPlan* ps, const void* in, void* out, int conj_in, int conj_out, double scale,
+                        hipStream_t s) {
+    const int f = ps[0].fuse;
+    BlockArgs a{};
+    a.in = in;
+    a.out = out;
+    a.naxes = f;
+    int tpl[3] = {1, 1, 1};
+    for (int i = 0; i < f; ++i) {
+        a.tw[i] = ps[i].tw;
+        a.kid[i] = block_case(ps[i].k);
+        if (a.kid[i] < 0) return hipErrorInvalidValue;
+        tpl[i] = block_case_of_length(ps[i].k->dtype, ps[i].L)->tpl;
+    }
+    a.C = ps[0].L;
+    a.B = ps[1].L;
+    a.A = f == 3 ? ps[2].L : 1;
+    a.pitch = block_pitch(a.C);
+    a.rcp_C = block_rcp(a.C);
+    a.stream_in = ps[0].stream;
+    a.stream_out = ps[f - 1].stream;
+    a.conj_in = conj_in;
+    a.conj_out = conj_out;
+    a.scale = scale;
+    const int64_t blocks = ps[f - 1].M1;
+    const int dtype = ps[0].k->dtype;
+    const int64_t n = (int64_t)a.A * a.B * a.C;
+    const int64_t lds = block_lds_elems(a.A, a.B, a.C) * (int64_t)elem_size(dtype);
+    if (lds > lds_limit()) return hipErrorInvalidValue;
+    // Threads: enough for every line of a pass at once, or, where there are
+    // more blocks than CUs and 1024 threads still reside on a CU, half of that
+    // (two rounds of lines).  3072 planes of 48 x 48, complex128: 112, 105, 94
+    // and 85 us a transform with 576, 320, 384 (one round) and 192 threads;
+    // 4096 planes of 64 x 64, two to a CU: 192 and 204 us with 512 and 256.
+    const int64_t one = std::max(std::max(n / a.C * tpl[0], n / a.B * tpl[1]), f == 3 ? n / a.A * tpl[2] : 0);
+    const int64_t per_cu = lds_limit() / lds;
+    int64_t want = one;
+    if (blocks > 256 && per_cu * ((one / 2 + 63) / 64 * 64) >= 1024) want = one / 2;
+    const int maxl = std::max(std::max(a.A, a.B), a.C);
+    for (const BlockKernel& bk : kBlockKernels) {
+        if (bk.dtype != dtype || maxl > bk.max_l) continue;
+        const int64_t least = std::max(std::max(tpl[0], tpl[1]), tpl[2]);
+        const int threads = (int)std::min<int64_t>(bk.threads, (std::max(want, least) + 63) / 64 * 64);
+        return bk.launch(a, blocks, threads, (size_t)lds, s);
+    }
+    return hipErrorInvalidValue;
 }
 
 hipError_t launch_pass(const PassPlan& p, const void* in, void* out, int conj_in, int conj_out,

@@ -124,6 +124,7 @@ static int time_passes(offt_plan_s* p, PassPlan* passes, int n, int64_t nelem, v
         if (!passes[i].k) return OFFT_ERR_UNSUPPORTED_SIZE;
     int rc = attach_twiddles(p, passes, n, s);
     if (rc != OFFT_SUCCESS) return rc;
+    if (p->allow_fuse) set_fuse(passes, n);   // timed as exec runs them
     // fresh random data per candidate: unnormalised transforms repeated in
     // place would otherwise grow the values towards overflow
     if (launch_fill_uniform(src, nelem, p->dtype, 1501, s) != hipSuccess) return OFFT_ERR_HIP;

@@ -47,7 +47,8 @@ def test_default_plans_follow_the_size_classes(gk, prec):
     def kernel(L, spec):
         return gk.parse_spec(L, spec.replace("/x", ""))
     es = 16 if prec == "f64" else 8
-    for shape in [(16, 20, 45), (32, 60, 64), (90, 100, 120), (128, 128, 96), (225, 320, 300), (512, 480, 450)]:
+    # rows longer than a block kernel's (256 points), so that every pass runs alone
+    for shape in [(16, 20, 270), (32, 60, 288), (90, 100, 300), (128, 128, 320), (225, 320, 300), (512, 480, 450)]:
         n = shape[0] * shape[1] * shape[2]
         limit = (256 if prec == "f64" else 192) << 20
         cls = 0 if n * es <= 8 << 20 else (1 if n * es <= limit else 2)
@@ -59,8 +60,8 @@ def test_default_plans_follow_the_size_classes(gk, prec):
 
 
 def test_few_lines_keep_the_rules_kernels(gk):
-    # 16 x 15 = 240 lines of 128 points against 16 x 16 = 256
-    few = _fields(offt.default_plan_string((16, 15, 128), torch.complex128))["c"]
-    many = _fields(offt.default_plan_string((16, 16, 128), torch.complex128))["c"]
-    assert few.split("/")[0] == "16x8"
-    assert gk.parse_spec(128, many) == gk.parse_spec(128, dict(((p, k, L), s) for p, k, L, s in gk.default_lines())[("f64", "c", 128)][0])
+    # 2 x 100 = 200 lines of 480 points against 3 x 100 = 300
+    few = _fields(offt.default_plan_string((2, 100, 480), torch.complex128))["c"]
+    many = _fields(offt.default_plan_string((3, 100, 480), torch.complex128))["c"]
+    assert few.split("/")[0] == "16x5x3x2"
+    assert gk.parse_spec(480, many) == gk.parse_spec(480, {(p, k, L): s for p, k, L, s in gk.default_lines()}[("f64", "c", 480)][0])
