@@ -7,11 +7,14 @@
 // arithmetic of every line is that of the stand-alone pass with the same
 // radix sequence, so the results have the same bits.
 //
-// LDS layout: row (a, b) starts at (a B + b) * pitch, its element c sits at
-// lds_idx(c) (one pad slot per 16, odd pitch, as in the pass tiles).  Lanes
-// walk along a row's butterflies in the pass over c and along columns in the
-// others.  Every thread does at most one butterfly of a stage (TPL = L / the
-// smallest radix threads per line).
+// LDS layout: element (a, b, c) sits at (a B + b) * pitch + c with an odd
+// pitch.  Lanes walk across lines in every pass (rows in the pass over c,
+// columns in the others), so a wave's accesses are pitch or one apart and
+// fall on different banks without padding, and one instantiation per line
+// length serves every axis: a block runs each instruction a few times only,
+// so that fetching its code is a good part of its time.  Every thread does at
+// most one butterfly of a stage (TPL = L / the smallest radix threads per
+// line).
 #pragma once
 
 #include "fft_device.hpp"
@@ -40,16 +43,13 @@ __host__ __device__ constexpr uint32_t block_rcp(int C) { return (uint32_t)((0x1
 __device__ __forceinline__ int block_div(int f, uint32_t rcp) { return (int)(((uint64_t)(uint32_t)f * rcp) >> 32); }
 
 // Elements of LDS: the rows, then the twiddle tables of the axes in use.
-__host__ __device__ constexpr int block_pitch(int C) { return (lds_idx(C - 1) + 1) | 1; }
+__host__ __device__ constexpr int block_pitch(int C) { return C | 1; }
 __host__ __device__ constexpr int64_t block_lds_elems(int A, int B, int C) {
     return (int64_t)A * B * block_pitch(C) + C + B + (A > 1 ? A : 0);
 }
 
-template <typename V> struct BlockRow {      // element j of a row
-    V* p;
-    __device__ __forceinline__ V& operator()(int j) const { return p[lds_idx(j)]; }
-};
-template <typename V> struct BlockColumn {   // element j of a line across rows
+// Element j of a line in LDS.
+template <typename V> struct BlockLine {
     V* p;
     int stride;
     __device__ __forceinline__ V& operator()(int j) const { return p[j * stride]; }
@@ -108,30 +108,16 @@ __device__ __forceinline__ void block_line(const At& at, const V* __restrict__ t
     block_stages<V, L, 1, R, Rest...>(v, at, tw, t, act, sink_lds, sink);
 }
 
-// The pass over c: every row of the block, blockDim / TPL rows at a time.
+// The pass over axis 0 (c), 1 (b) or 2 (a): blockDim / TPL lines at a time,
+// lanes on consecutive lines.  The last pass writes the block to HBM.
 template <typename V, int L, int TPL, int... Rs>
-__device__ __forceinline__ void block_rows(const BlockArgs& a, V* __restrict__ lds, const V* __restrict__ tw, int tid) {
-    const int rows = a.A * a.B, per = (int)blockDim.x / TPL;
-    const int w = tid / TPL, t = tid - w * TPL;
-#pragma unroll 1
-    for (int r0 = 0; r0 < rows; r0 += per) {
-        const bool act = w < per && r0 + w < rows;
-        const BlockRow<V> at{lds + (act ? r0 + w : 0) * a.pitch};
-        auto sink = [&](int j, V x) { at(j) = x; };
-        block_line<V, L, Rs...>(at, tw, t, act, true, sink);
-    }
-}
-
-// The pass over b (axis 1) or a (axis 2): blockDim / TPL lines at a time,
-// lanes on consecutive columns.  The last pass writes the block to HBM.
-template <typename V, int L, int TPL, int... Rs>
-__device__ __forceinline__ void block_columns(const BlockArgs& a, V* __restrict__ lds, const V* __restrict__ tw,
-                                              V* __restrict__ go, int axis, int tid) {
+__device__ __forceinline__ void block_pass(const BlockArgs& a, V* __restrict__ lds, const V* __restrict__ tw,
+                                           V* __restrict__ go, int axis, int tid) {
     using S = decltype(V{}.x);
     const bool last = axis == a.naxes - 1;
-    const int lines = (axis == 1 ? a.A : a.B) * a.C, per = (int)blockDim.x / TPL;
-    const int stride = axis == 1 ? a.pitch : a.B * a.pitch;      // LDS
-    const int outer = axis == 1 ? a.B * a.pitch : a.pitch;      // from one row of lines to the next
+    const int lines = axis == 0 ? a.A * a.B : (axis == 1 ? a.A : a.B) * a.C, per = (int)blockDim.x / TPL;
+    const int stride = axis == 0 ? 1 : (axis == 1 ? a.pitch : a.B * a.pitch);
+    const int outer = axis == 1 ? a.B * a.pitch : a.pitch;   // from one row of lines to the next
     const int gstride = axis == 1 ? a.C : a.B * a.C;
     const int t = tid / per, w = tid - t * per;
     const S scale = (S)a.scale;
@@ -139,8 +125,13 @@ __device__ __forceinline__ void block_columns(const BlockArgs& a, V* __restrict_
     for (int l0 = 0; l0 < lines; l0 += per) {
         const int l = l0 + w;
         const bool act = t < TPL && l < lines;
-        const int o = act ? block_div(l, a.rcp_C) : 0, c = act ? l - o * a.C : 0;
-        const BlockColumn<V> at{lds + o * outer + lds_idx(c), stride};
+        int o = act ? l : 0, c = 0;      // rows: line l is row l
+        if (axis > 0) {
+            const int q = block_div(o, a.rcp_C);
+            c = o - q * a.C;
+            o = q;
+        }
+        const BlockLine<V> at{lds + o * outer + c, stride};
         auto sink = [&](int j, V x) {
             if (last) store_io(go + (int64_t)l + (int64_t)j * gstride, fix_out(x, a.conj_out, scale), a.stream_out != 0);
             else at(j) = x;
@@ -149,11 +140,10 @@ __device__ __forceinline__ void block_columns(const BlockArgs& a, V* __restrict_
     }
 }
 
-// One block: load, pass over c, pass over b, pass over a.  Rows and Columns
-// run the kernel case of their axis.
-template <typename V, typename Rows, typename Columns>
-__device__ __forceinline__ void block_body(const BlockArgs& a, V* __restrict__ lds, int64_t block, const Rows& rows,
-                                           const Columns& columns) {
+// One block: load, then the passes over c, b and a.  Pass runs the kernel
+// case of an axis.
+template <typename V, typename Pass>
+__device__ __forceinline__ void block_body(const BlockArgs& a, V* __restrict__ lds, int64_t block, const Pass& pass) {
     const int tid = (int)threadIdx.x, T = (int)blockDim.x;
     const int n = a.A * a.B * a.C;
     const V* g = static_cast<const V*>(a.in) + block * n;
@@ -173,7 +163,7 @@ __device__ __forceinline__ void block_body(const BlockArgs& a, V* __restrict__ l
             const int f = f0 + u * T;
             if (f < n) {
                 const int r = block_div(f, a.rcp_C);
-                lds[r * a.pitch + lds_idx(f - r * a.C)] = fix_in(x[u], a.conj_in);
+                lds[r * a.pitch + f - r * a.C] = fix_in(x[u], a.conj_in);
             }
         }
     }
@@ -183,20 +173,13 @@ __device__ __forceinline__ void block_body(const BlockArgs& a, V* __restrict__ l
         for (int i = tid; i < len[ax]; i += T) twk[i] = src[i];
         twk += len[ax];
     }
-    __syncthreads();
-    {
-        int id = tid;
-        OFFT_OPAQUE_VGPR(id);   // each case's index math stays in its pass
-        rows(a, lds, tw, id);
-    }
-    V* twx = tw + a.C;
 #pragma unroll 1
-    for (int ax = 1; ax < a.naxes; ++ax) {
+    for (int ax = 0; ax < a.naxes; ++ax) {
         __syncthreads();
         int id = tid;
-        OFFT_OPAQUE_VGPR(id);
-        columns(a, lds, twx, go, ax, id);
-        twx += a.B;
+        OFFT_OPAQUE_VGPR(id);   // each case's index math stays in its pass
+        pass(a, lds, tw, go, ax, id);
+        tw += ax == 0 ? a.C : a.B;
     }
 }
 

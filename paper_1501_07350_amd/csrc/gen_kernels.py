@@ -257,22 +257,17 @@ def emit_block(outdir):
                      '#include "fft_block.hpp"',
                      "namespace offt {",
                      "namespace {",
-                     "struct Rows {",
-                     f"    __device__ __forceinline__ void operator()(const BlockArgs& a, {vt}* lds, const {vt}* tw, int tid) const {{",
-                     "        switch (a.kid[0]) {"]
-            used = [(i, c) for i, c in enumerate(cases) if c[0] <= max_l]
-            for i, (L, seq, tpl) in used:
-                lines.append(f"            case {i}: block_rows<{vt}, {L}, {tpl}, {', '.join(map(str, seq))}>(a, lds, tw, tid); break;")
-            lines += ["            default: break;", "        }", "    }", "};", "struct Columns {",
-                      f"    __device__ __forceinline__ void operator()(const BlockArgs& a, {vt}* lds, const {vt}* tw, {vt}* go, "
-                      "int axis, int tid) const {",
-                      "        switch (axis == 1 ? a.kid[1] : a.kid[2]) {"]
-            for i, (L, seq, tpl) in used:
-                lines.append(f"            case {i}: block_columns<{vt}, {L}, {tpl}, {', '.join(map(str, seq))}>(a, lds, tw, go, axis, tid); break;")
+                     "struct Pass {",
+                     f"    __device__ __forceinline__ void operator()(const BlockArgs& a, {vt}* lds, const {vt}* tw, {vt}* go, "
+                     "int axis, int tid) const {",
+                     "        switch (a.kid[axis]) {"]
+            for i, (L, seq, tpl) in enumerate(cases):
+                if L <= max_l:
+                    lines.append(f"            case {i}: block_pass<{vt}, {L}, {tpl}, {', '.join(map(str, seq))}>(a, lds, tw, go, axis, tid); break;")
             lines += ["            default: break;", "        }", "    }", "};",
                       f"__global__ void __launch_bounds__({threads}) {attr}fft_block_{name}_{prec}(BlockArgs a) {{",
                       "    extern __shared__ __align__(16) unsigned char smem_raw[];",
-                      f"    block_body<{vt}>(a, reinterpret_cast<{vt}*>(smem_raw), (int64_t)blockIdx.x, Rows{{}}, Columns{{}});",
+                      f"    block_body<{vt}>(a, reinterpret_cast<{vt}*>(smem_raw), (int64_t)blockIdx.x, Pass{{}});",
                       "}",
                       "}  // namespace",
                       f"hipError_t launch_block_{name}_{prec}(const BlockArgs& a, int64_t nblocks, int threads, size_t lds, "

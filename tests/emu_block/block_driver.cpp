@@ -69,7 +69,7 @@ template <typename V> static int run(char** v) {
             th.emplace_back([&, t] {
                 threadIdx.x = t;
                 g_emu_barrier_count = 0;
-                block_body<V>(a, lds.data(), b, EmuRows<V>{}, EmuColumns<V>{});
+                block_body<V>(a, lds.data(), b, EmuPass<V>{});
                 barriers[t] = g_emu_barrier_count;
             });
         for (auto& x : th) x.join();

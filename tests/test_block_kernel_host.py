@@ -31,17 +31,12 @@ def gk():
 
 @pytest.fixture(scope="module")
 def driver(gk):
-    text = "namespace offt {\n"
-    for name, fn, extra, args in (("EmuRows", "block_rows", "int tid", "tid"),
-                                  ("EmuColumns", "block_columns", "V* go, int axis, int tid", "go, axis, tid")):
-        sel = "a.kid[0]" if name == "EmuRows" else "(axis == 1 ? a.kid[1] : a.kid[2])"
-        text += (f"template <typename V> struct {name} {{ void operator()(const BlockArgs& a, V* lds, const V* tw, {extra}) "
-                 f"const {{ switch ({sel}) {{\n")
-        for L in LENGTHS:
-            seq = gk.block_seq(L)
-            text += f"case {L}: {fn}<V, {L}, {L // min(seq)}, {', '.join(map(str, seq))}>(a, lds, tw, {args}); break;\n"
-        text += "default: break; } } };\n"
-    text += "}\n"
+    text = ("namespace offt {\ntemplate <typename V> struct EmuPass { void operator()(const BlockArgs& a, V* lds, const V* tw, "
+            "V* go, int axis, int tid) const { switch (a.kid[axis]) {\n")
+    for L in LENGTHS:
+        seq = gk.block_seq(L)
+        text += f"case {L}: block_pass<V, {L}, {L // min(seq)}, {', '.join(map(str, seq))}>(a, lds, tw, go, axis, tid); break;\n"
+    text += "default: break; } } };\n}\n"
     h = hashlib.sha256(text.encode())
     for p in (DRIVER, os.path.join(EMU, "hip_emu.h"), os.path.join(CSRC, "fft_block.hpp"), os.path.join(CSRC, "fft_device.hpp")):
         h.update(open(p, "rb").read())
