@@ -430,6 +430,10 @@ __device__ __forceinline__ void exchange(V* __restrict__ line, int t, bool act, 
 template <typename S, typename = void> struct SinkParts { static constexpr int value = 1; };
 template <typename S> struct SinkParts<S, decltype((void)S::kParts)> { static constexpr int value = S::kParts; };
 
+template <typename S> struct IsLineSink;
+template <bool NT, typename V, int L, int TPL, int R, typename Sink>
+__device__ __forceinline__ void put_outputs(StageRegs<V, L, TPL, R>& v, int t, bool act, Sink& sink);
+
 // The last stage's outputs j = b + r*L/R to the sink.  Output j lies in part
 // r div (R/kParts) when kParts divides R.
 template <typename V, int L, int TPL, int R, typename Sink>
@@ -437,6 +441,13 @@ __device__ __forceinline__ void emit_outputs(StageRegs<V, L, TPL, R>& v, int t, 
     using SH = StageShape<V, L, TPL, R>;
     constexpr int OP = SinkParts<Sink>::value;
     static_assert(R % OP == 0, "the last radix must split into the sink's parts");
+    if constexpr (IsLineSink<Sink>::value) {
+        if (!sink.ok) return;
+        if (sink.nt) put_outputs<true, V, L, TPL, R>(v, t, act, sink);
+        else put_outputs<false, V, L, TPL, R>(v, t, act, sink);
+        return;
+    }
+    else
 #pragma unroll
     for (int p = 0; p < OP; ++p) {
 #pragma unroll
@@ -483,6 +494,61 @@ __device__ __forceinline__ void stage_regs(StageRegs<V, L, TPL, R>& v, V* __rest
         exchange<V, L, TPL, P, NS, R, R2>(line, t, act, v, u);
         stage_regs<V, L, TPL, P, NS * R, Rest...>(u, line, tw, t, act, sink);
     }
+}
+
+// Applies fn to the first-stage inputs that load_first filled.
+template <typename V, int L, int TPL, int R, typename Fn>
+__device__ __forceinline__ void map_first(StageRegs<V, L, TPL, R>& v, int t, bool act, Fn fn) {
+    using SH = StageShape<V, L, TPL, R>;
+#pragma unroll
+    for (int i = 0; i < SH::NB; ++i) {
+        const int b = t + i * TPL;
+        if (act && (SH::EXACT || b < SH::B)) {
+#pragma unroll
+            for (int r = 0; r < R; ++r) v[i][r] = fn(v[i][r]);
+        }
+    }
+}
+
+// Staging of the twiddle table W_L^m (m < L) in LDS; the first barrier after
+// the first stage, which needs no twiddles, orders it before any use.  A pass
+// over little data overlaps it with the tile's own loads: begin issues the
+// loads of a thread's first two entries (the last entry where there are fewer:
+// no branch, so that nothing waits for them here), finish, after the tile's
+// loads, writes them to LDS and copies the rest (tiles of few lines).  128^3
+// complex128: 75.4 -> 72.5 us a round trip; 8 x 48x60x50 complex64: 17.7 ->
+// 16.5 us.  With first = true, begin stages the whole table before the tile's
+// loads; passes bound by HBM do that, since with the loads first several lost
+// 12 to 30% (512^3 complex128 in 256 MiB slabs, pass c: 83 -> 94 us; 512^3
+// complex128 streaming, pass b: 0.69 -> 0.79 ms; 1024^3 complex64, pass c:
+// 2.66 -> 3.44 ms).
+constexpr int64_t kOverlapBytes = int64_t(64) << 20;
+template <typename V, int L>
+__device__ __forceinline__ void twiddles_begin(V& x0, V& x1, V* __restrict__ dst, const V* __restrict__ src, int tid, bool first) {
+    const int T = (int)blockDim.x;
+    if (first) {
+        for (int i = tid; i < L; i += T) dst[i] = src[i];
+        x0 = V{};
+        x1 = V{};
+    } else {
+        x0 = src[tid < L ? tid : L - 1];
+        x1 = src[tid + T < L ? tid + T : L - 1];
+    }
+}
+template <typename V, int L>
+__device__ __forceinline__ void twiddles_finish(V* __restrict__ dst, V x0, V x1, const V* __restrict__ src, int tid, bool first) {
+    if (first) return;
+    const int T = (int)blockDim.x;
+    if (tid < L) dst[tid] = x0;
+    if (tid + T < L) dst[tid + T] = x1;
+    for (int i = tid + 2 * T; i < L; i += T) dst[i] = src[i];
+}
+
+// Quotient of line indexes; almost every pass has fewer than 2^32 lines, whose
+// 32-bit division takes a fraction of the 64-bit one's instructions.
+__device__ __forceinline__ int64_t line_div(int64_t l, int64_t d, int64_t nlines) {
+    if (nlines <= 0xffffffff && d <= 0xffffffff) return (int64_t)((uint32_t)l / (uint32_t)d);
+    return l / d;
 }
 
 // First-stage inputs of the thread's butterflies: v[i][r] = src(b + r*L/R).
@@ -625,6 +691,20 @@ template <typename V> __device__ __forceinline__ void store_io(V* p, V v, bool n
     else *p = v;
 }
 
+// load_first from g[j * stride] in HBM; one branch on the access mode around
+// all loads.
+template <typename V, int L, int TPL, int R>
+__device__ __forceinline__ void load_first_io(StageRegs<V, L, TPL, R>& v, int t, bool act, const V* __restrict__ g,
+                                              int64_t stride, bool nt) {
+    if (nt) {
+        auto src = [&](int j) { return load_stream(g + (int64_t)j * stride); };
+        load_first<V, L, TPL, R>(v, t, act, src);
+    } else {
+        auto src = [&](int j) { return g[(int64_t)j * stride]; };
+        load_first<V, L, TPL, R>(v, t, act, src);
+    }
+}
+
 // Store of one element to HBM.  COHERENT stores are agent-scope relaxed
 // atomics: they write through the XCD's L2, so data another workgroup will
 // read after a release/acquire handshake never sits dirty in one L2 and the
@@ -656,6 +736,38 @@ template <bool COHERENT, typename V> __device__ __forceinline__ void store_elem_
     else store_io(p, x, nt);
 }
 
+// Last-stage sink to g[j * stride] in HBM; emit_outputs takes its branches
+// (a line beyond the tile's last stores nothing; access mode) once around all
+// stores.
+template <typename V, bool COHERENT> struct LineSink {
+    using S = decltype(V{}.x);
+    V* g;
+    int64_t stride;
+    bool ok, nt;
+    int cout;
+    S scale;
+    template <bool NT> __device__ __forceinline__ void put(int j, V x) {
+        const V y = fix_out(x, cout, scale);
+        if constexpr (COHERENT) store_elem<true>(g + (int64_t)j * stride, y);
+        else if constexpr (NT) store_stream(g + (int64_t)j * stride, y);
+        else g[(int64_t)j * stride] = y;
+    }
+};
+template <typename S> struct IsLineSink { static constexpr bool value = false; };
+template <typename V, bool C> struct IsLineSink<LineSink<V, C>> { static constexpr bool value = true; };
+template <bool NT, typename V, int L, int TPL, int R, typename Sink>
+__device__ __forceinline__ void put_outputs(StageRegs<V, L, TPL, R>& v, int t, bool act, Sink& sink) {
+    using SH = StageShape<V, L, TPL, R>;
+#pragma unroll
+    for (int i = 0; i < SH::NB; ++i) {
+        const int b = t + i * TPL;
+        if (act && (SH::EXACT || b < SH::B)) {
+#pragma unroll
+            for (int r = 0; r < R; ++r) sink.template put<NT>(b + r * SH::B, v[i][r]);
+        }
+    }
+}
+
 // Contiguous lines with fewer than this many threads per line are staged
 // through LDS with a flat coalesced copy (direct loads would touch one
 // element per line per lane).
@@ -683,9 +795,14 @@ __device__ __forceinline__ int tile_thread_index() {
 //   contiguous lines:  lanes walk along the line; first/last stage straight
 //                      from/to HBM when TPL >= kDirectRowMinTpl, else the tile
 //                      is staged through LDS as one contiguous block.
+// OVERLAP (stand-alone passes): the twiddle table and the rows of a staged
+// block are loaded with all of a thread's loads in flight; the batch executors
+// keep one element at a time, because the registers of all their cases together
+// decide how many of their workgroups reside (64 complex64 grids, level
+// kernels: 688 us with 64 registers, 735 us with the 93 of the other form).
 // Threads beyond W*TPL (possible when a larger workgroup runs this tile, as in
 // the persistent batch executor) only take part in the barriers.
-template <typename V, bool COHERENT, bool LOOPED, int L, int TPL, int P, int... Rs>
+template <typename V, bool COHERENT, bool LOOPED, bool OVERLAP, int L, int TPL, int P, int... Rs>
 __device__ __forceinline__ void pass_tile_impl(const PassArgs& a, V* __restrict__ lds, int64_t l0) {
     using S = decltype(V{}.x);
     static_assert(RadixProduct<Rs...>::value == L, "radix sequence must multiply to L");
@@ -701,20 +818,20 @@ __device__ __forceinline__ void pass_tile_impl(const PassArgs& a, V* __restrict_
     const S scale = (S)a.scale;
     const bool active = tid < W * TPL;
     const bool nt = !COHERENT && a.stream_io;
-    if constexpr (sizeof...(Rs) > 1) {
-        // stage the twiddle table; the first barrier inside run_fft (after the
-        // first stage, which needs no twiddles) orders it before any use
-        V* twl = lds + W * LP;
-        for (int i = tid; i < L; i += (int)blockDim.x) twl[i] = tw[i];
-        tw = twl;
-    }
+    constexpr int R0 = FirstRadix<Rs...>::value;
+    constexpr bool kTwiddles = sizeof...(Rs) > 1;
+    const bool tw_first = !OVERLAP || a.nlines * (int64_t)(L * sizeof(V)) > kOverlapBytes;
+    V tw0, tw1;
+    V* const twl = lds + W * LP;
+    if constexpr (kTwiddles) twiddles_begin<V, L>(tw0, tw1, twl, tw, tid, tw_first);
+    auto fix = [&](V x) { return fix_in(x, cin); };
 
     if (a.mode == 1) {
         const int w = tid & (W - 1);
         const int t = tid >> a.logW;
         const bool ok = active && w < nl;
         const int64_t l = l0 + (ok ? w : 0);   // rows beyond the tail read line l0, store nothing
-        const int64_t m1 = l / a.lpm, v = l - m1 * a.lpm;
+        const int64_t m1 = line_div(l, a.lpm, a.nlines), v = l - m1 * a.lpm;
         const int64_t m2 = a.blk_logw < 0 ? v
                                           : (v >> a.blk_logw) * a.blk_ld + a.blk_off +
                                                 (v & ((int64_t(1) << a.blk_logw) - 1));
@@ -722,11 +839,12 @@ __device__ __forceinline__ void pass_tile_impl(const PassArgs& a, V* __restrict_
         const int64_t M2 = a.M2;
         const V* g = in + base;
         V* go = out + base;
-        auto src = [&](int j) { return fix_in(load_elem<COHERENT>(g + (int64_t)j * M2, nt), cin); };
-        auto sink = [&](int j, V x) {
-            if (ok) store_elem_io<COHERENT>(go + (int64_t)j * M2, fix_out(x, cout, scale), nt);
-        };
-        run_fft<V, L, TPL, P, false, false, Rs...>(lds + w * LP, tw, t, active, src, sink);
+        LineSink<V, COHERENT> sink{go, M2, ok, nt, cout, scale};
+        StageRegs<V, L, TPL, R0> x;
+        load_first_io<V, L, TPL, R0>(x, t, active, g, M2, nt);
+        if constexpr (kTwiddles) twiddles_finish<V, L>(twl, tw0, tw1, tw, tid, tw_first);
+        map_first<V, L, TPL, R0>(x, t, active, fix);
+        fft_from_regs<V, L, TPL, P, false, false, Rs...>(x, lds + w * LP, twl, t, active, sink);
         return;
     }
     // contiguous lines keep whole lines in LDS: kernels with parts serve strided lines only
@@ -737,31 +855,65 @@ __device__ __forceinline__ void pass_tile_impl(const PassArgs& a, V* __restrict_
             const bool ok = active && tid / TPL < nl;
             const V* g = in + (l0 + (ok ? w : 0)) * L;
             V* go = out + (l0 + w) * L;
-            auto src = [&](int j) { return fix_in(load_elem<COHERENT>(g + j, nt), cin); };
+            // (stores one by one: with the branch around all of them, as in
+            // LineSink, pass c of 1024^3 complex64 took 2.75 ms instead of 2.69)
             auto sink = [&](int j, V x) {
                 if (ok) store_elem_io<COHERENT>(go + j, fix_out(x, cout, scale), nt);
             };
-            run_fft<V, L, TPL, 1, false, false, Rs...>(line, tw, t, active, src, sink);
+            StageRegs<V, L, TPL, R0> x;
+            load_first_io<V, L, TPL, R0>(x, t, active, g, 1, nt);
+            if constexpr (kTwiddles) twiddles_finish<V, L>(twl, tw0, tw1, tw, tid, tw_first);
+            map_first<V, L, TPL, R0>(x, t, active, fix);
+            fft_from_regs<V, L, TPL, 1, false, false, Rs...>(x, line, twl, t, active, sink);
         } else {
-            // stage the contiguous block of nl*L elements through LDS
+            // stage the contiguous block of nl*L elements through LDS, with
+            // all of a thread's loads in flight at once (f = tid + k NT, k < K)
             const int NT = W * TPL;
+            constexpr int K = (L + TPL - 1) / TPL;
             const V* g = in + l0 * L;
             V* go = out + l0 * L;
-            if (active) {
-                for (int f = tid; f < nl * L; f += NT) {
-                    const int lw = f / L, j = f - lw * L;
-                    lds[lw * LP + lds_idx(j)] = fix_in(load_elem<COHERENT>(g + f, nt), cin);
+            if constexpr (!OVERLAP) {
+                if (active) {
+                    for (int f = tid; f < nl * L; f += NT) {
+                        const int lw = f / L, j = f - lw * L;
+                        lds[lw * LP + lds_idx(j)] = fix(load_elem<COHERENT>(g + f, nt));
+                    }
+                }
+            } else {
+                V x[K];
+#pragma unroll
+                for (int k = 0; k < K; ++k)
+                    if (active && tid + k * NT < nl * L) x[k] = load_io(g + tid + k * NT, nt);
+                if constexpr (kTwiddles) twiddles_finish<V, L>(twl, tw0, tw1, tw, tid, tw_first);
+#pragma unroll
+                for (int k = 0; k < K; ++k) {
+                    const int f = tid + k * NT;
+                    if (active && f < nl * L) {
+                        const int lw = f / L, j = f - lw * L;
+                        lds[lw * LP + lds_idx(j)] = fix(x[k]);
+                    }
                 }
             }
             __syncthreads();
             auto src = [&](int j) { return line[lds_idx(j)]; };
             auto sink = [&](int j, V x) { line[lds_idx(j)] = x; };
-            run_fft<V, L, TPL, 1, true, true, Rs...>(line, tw, t, active, src, sink);
+            run_fft<V, L, TPL, 1, true, true, Rs...>(line, twl, t, active, src, sink);
             __syncthreads();
-            if (active) {
-                for (int f = tid; f < nl * L; f += NT) {
-                    const int lw = f / L, j = f - lw * L;
-                    store_elem_io<COHERENT>(go + f, fix_out(lds[lw * LP + lds_idx(j)], cout, scale), nt);
+            if constexpr (!OVERLAP) {
+                if (active) {
+                    for (int f = tid; f < nl * L; f += NT) {
+                        const int lw = f / L, j = f - lw * L;
+                        store_elem_io<COHERENT>(go + f, fix_out(lds[lw * LP + lds_idx(j)], cout, scale), nt);
+                    }
+                }
+            } else {
+#pragma unroll
+                for (int k = 0; k < K; ++k) {
+                    const int f = tid + k * NT;
+                    if (active && f < nl * L) {
+                        const int lw = f / L, j = f - lw * L;
+                        store_io(go + f, fix_out(lds[lw * LP + lds_idx(j)], cout, scale), nt);
+                    }
                 }
             }
         }
@@ -771,7 +923,7 @@ __device__ __forceinline__ void pass_tile_impl(const PassArgs& a, V* __restrict_
 // Row-side stores of a transposing pass whose last stage emits in P parts:
 // part p of every line goes to its line's LDS slots, then the W half (or
 // quarter) rows leave with a flat coalesced copy.
-template <typename V, int L, int P>
+template <typename V, int L, int TPL, int P>
 struct RowPartSink {
     static constexpr int kParts = P;
     static constexpr int PART = L / P;
@@ -789,9 +941,13 @@ struct RowPartSink {
     }
     __device__ __forceinline__ void flush(int p) {
         if (!active) return;
-        for (int f = tid; f < nl * PART; f += nt) {
-            const int lw = f / PART, jj = f - lw * PART;
-            store_io(out + rows[lw] + p * PART + jj, lds[lw * LP + lds_idx(jj)], stream);
+#pragma unroll
+        for (int k = 0; k < (PART + TPL - 1) / TPL; ++k) {
+            const int f = tid + k * nt;
+            if (f < nl * PART) {
+                const int lw = f / PART, jj = f - lw * PART;
+                store_io(out + rows[lw] + p * PART + jj, lds[lw * LP + lds_idx(jj)], stream);
+            }
         }
     }
 };
@@ -827,16 +983,20 @@ __device__ __forceinline__ void pass_tile_transpose(const PassArgs& a, V* __rest
     const bool active = tid < NT;
     const bool nts = a.stream_io != 0;
     const int64_t M2 = a.M2;
-    if constexpr (sizeof...(Rs) > 1) {
-        V* twl = lds + W * LP;
-        for (int i = tid; i < L; i += (int)blockDim.x) twl[i] = tw[i];
-        tw = twl;
-    }
+    constexpr int R0 = FirstRadix<Rs...>::value;
+    // twiddles staged around the tile's first loads (pass_tile_impl)
+    constexpr bool kTwiddles = sizeof...(Rs) > 1;
+    const bool tw_first = a.nlines * (int64_t)(L * sizeof(V)) > kOverlapBytes;
+    V tw0, tw1;
+    V* const twl = lds + W * LP;
+    if constexpr (kTwiddles) twiddles_begin<V, L>(tw0, tw1, twl, tw, tid, tw_first);
+    auto fix = [&](V x) { return fix_in(x, cin); };
+    constexpr int K = (PART + TPL - 1) / TPL;   // row-side elements per thread and part
     // element offset of each line's row in the row-side buffer
     int64_t* rows = reinterpret_cast<int64_t*>(lds + W * LP + L);
     if (tid < nl) {
         const int64_t l = l0 + tid;
-        const int64_t m1 = l / M2, m2 = l - m1 * M2;
+        const int64_t m1 = line_div(l, M2, a.nlines), m2 = l - m1 * M2;
         rows[tid] = (m1 * M2 + (m2 % a.X) * a.Y + m2 / a.X) * (int64_t)L;
     }
     __syncthreads();
@@ -844,38 +1004,47 @@ __device__ __forceinline__ void pass_tile_transpose(const PassArgs& a, V* __rest
     const int t = tid >> a.logW;
     const bool ok = active && w < nl;
     const int64_t l = l0 + (ok ? w : 0);   // rows beyond the tail compute on line l0, store nothing
-    const int64_t m1 = l / M2, m2 = l - m1 * M2;
+    const int64_t m1 = line_div(l, M2, a.nlines), m2 = l - m1 * M2;
     const int64_t base = m1 * (int64_t)L * M2 + m2;
     V* line = lds + w * LP;
     if (a.mode == 2) {
         V* go = out + base;
-        auto sink = [&](int j, V x) {
-            if (ok) store_io(go + (int64_t)j * M2, fix_out(x, cout, scale), nts);
-        };
+        LineSink<V, false> sink{go, M2, ok, nts, cout, scale};
         if constexpr (P == 1) {
-            if (active) {
-                for (int f = tid; f < nl * L; f += NT) {
-                    const int lw = f / L, j = f - lw * L;
-                    lds[lw * LP + lds_idx(j)] = fix_in(load_io(in + rows[lw] + j, nts), cin);
-                }
+            V x[K];
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                const int f = tid + k * NT;
+                if (active && f < nl * L) x[k] = load_io(in + rows[f / L] + f % L, nts);
+            }
+            if constexpr (kTwiddles) twiddles_finish<V, L>(twl, tw0, tw1, tw, tid, tw_first);
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                const int f = tid + k * NT;
+                if (active && f < nl * L) lds[(f / L) * LP + lds_idx(f % L)] = fix(x[k]);
             }
             __syncthreads();
             auto src = [&](int j) { return line[lds_idx(j)]; };
-            run_fft<V, L, TPL, 1, true, false, Rs...>(line, tw, t, active, src, sink);
+            run_fft<V, L, TPL, 1, true, false, Rs...>(line, twl, t, active, src, sink);
         } else {
             // the first stage's inputs part by part: input j = b + r*L/R0
             // lies in part r div (R0/P)
-            constexpr int R0 = FirstRadix<Rs...>::value;
             static_assert(R0 % P == 0, "the first radix must split into the parts");
             using SH = StageShape<V, L, TPL, R0>;
             StageRegs<V, L, TPL, R0> v;
 #pragma unroll
             for (int p = 0; p < P; ++p) {
-                if (active) {
-                    for (int f = tid; f < nl * PART; f += NT) {
-                        const int lw = f / PART, jj = f - lw * PART;
-                        lds[lw * LP + lds_idx(jj)] = fix_in(load_io(in + rows[lw] + p * PART + jj, nts), cin);
-                    }
+                V x[K];
+#pragma unroll
+                for (int k = 0; k < K; ++k) {
+                    const int f = tid + k * NT;
+                    if (active && f < nl * PART) x[k] = load_io(in + rows[f / PART] + p * PART + f % PART, nts);
+                }
+                if (kTwiddles && p == 0) twiddles_finish<V, L>(twl, tw0, tw1, tw, tid, tw_first);
+#pragma unroll
+                for (int k = 0; k < K; ++k) {
+                    const int f = tid + k * NT;
+                    if (active && f < nl * PART) lds[(f / PART) * LP + lds_idx(f % PART)] = fix(x[k]);
                 }
                 __syncthreads();
 #pragma unroll
@@ -889,53 +1058,56 @@ __device__ __forceinline__ void pass_tile_transpose(const PassArgs& a, V* __rest
                 }
                 __syncthreads();
             }
-            fft_from_regs<V, L, TPL, P, false, false, Rs...>(v, line, tw, t, active, sink);
+            fft_from_regs<V, L, TPL, P, false, false, Rs...>(v, line, twl, t, active, sink);
         }
     } else {
         const V* g = in + base;
-        auto src = [&](int j) { return fix_in(load_io(g + (int64_t)j * M2, nts), cin); };
+        StageRegs<V, L, TPL, R0> x;
+        load_first_io<V, L, TPL, R0>(x, t, active, g, M2, nts);
+        if constexpr (kTwiddles) twiddles_finish<V, L>(twl, tw0, tw1, tw, tid, tw_first);
+        map_first<V, L, TPL, R0>(x, t, active, fix);
         if constexpr (P == 1) {
             auto sink = [&](int j, V x) { line[lds_idx(j)] = fix_out(x, cout, scale); };
-            run_fft<V, L, TPL, 1, false, true, Rs...>(line, tw, t, active, src, sink);
+            fft_from_regs<V, L, TPL, 1, false, true, Rs...>(x, line, twl, t, active, sink);
             __syncthreads();
-            if (active) {
-                for (int f = tid; f < nl * L; f += NT) {
-                    const int lw = f / L, j = f - lw * L;
-                    store_io(out + rows[lw] + j, lds[lw * LP + lds_idx(j)], nts);
-                }
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                const int f = tid + k * NT;
+                if (active && f < nl * L) store_io(out + rows[f / L] + f % L, lds[(f / L) * LP + lds_idx(f % L)], nts);
             }
         } else {
-            RowPartSink<V, L, P> sink{line, lds, out, rows, nl, tid, NT, cout, scale, active, nts};
-            run_fft<V, L, TPL, P, false, true, Rs...>(line, tw, t, active, src, sink);
+            RowPartSink<V, L, TPL, P> sink{line, lds, out, rows, nl, tid, NT, cout, scale, active, nts};
+            fft_from_regs<V, L, TPL, P, false, true, Rs...>(x, line, twl, t, active, sink);
         }
     }
 }
 
-// One tile of an axis pass with ordinary stores (stand-alone pass kernels).
+// One tile of an axis pass with ordinary stores (the batch executors' level
+// kernels).
 template <typename V, int L, int TPL, int... Rs>
 __device__ __forceinline__ void pass_tile(const PassArgs& a, V* __restrict__ lds, int64_t l0) {
-    pass_tile_impl<V, false, false, L, TPL, 1, Rs...>(a, lds, l0);
+    pass_tile_impl<V, false, false, false, L, TPL, 1, Rs...>(a, lds, l0);
 }
 
-// One tile of a strided pass whose LDS exchanges run in P parts (stand-alone
-// pass kernels of lengths whose radix sequence allows it).
+// One tile of a stand-alone pass kernel, LDS exchanges in P parts (P > 1:
+// strided passes of lengths whose radix sequence allows it).
 template <typename V, int L, int TPL, int P, int... Rs>
 __device__ __forceinline__ void pass_tile_parts(const PassArgs& a, V* __restrict__ lds, int64_t l0) {
-    pass_tile_impl<V, false, false, L, TPL, P, Rs...>(a, lds, l0);
+    pass_tile_impl<V, false, false, true, L, TPL, P, Rs...>(a, lds, l0);
 }
 
 // One tile with write-through stores (batch executors, whose tiles are read
 // by other workgroups of the same launch).
 template <typename V, int L, int TPL, int... Rs>
 __device__ __forceinline__ void pass_tile_coherent(const PassArgs& a, V* __restrict__ lds, int64_t l0) {
-    pass_tile_impl<V, true, false, L, TPL, 1, Rs...>(a, lds, l0);
+    pass_tile_impl<V, true, false, false, L, TPL, 1, Rs...>(a, lds, l0);
 }
 
 // One tile with ordinary stores inside a loop over tiles of every kernel
 // case (the level-synchronous batch executor).
 template <typename V, int L, int TPL, int... Rs>
 __device__ __forceinline__ void pass_tile_looped(const PassArgs& a, V* __restrict__ lds, int64_t l0) {
-    pass_tile_impl<V, false, true, L, TPL, 1, Rs...>(a, lds, l0);
+    pass_tile_impl<V, false, true, false, L, TPL, 1, Rs...>(a, lds, l0);
 }
 
 }  // namespace offt
