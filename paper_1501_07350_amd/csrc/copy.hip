@@ -42,11 +42,11 @@ __global__ void __launch_bounds__(MAXT) copy_pattern_kernel(CopyArgs a) {
     const int64_t l0 = xcd_tile(blockIdx.x, gridDim.x, a.xcd_remap) << a.logW;
     const int64_t rem = a.nlines - l0;
     const int nl = rem < W ? (int)rem : W;
-    const bool nt = a.stream_io != 0;
+    const bool nt = a.stream_io & kStreamLoads, nts = a.stream_io & kStreamStores;
     if (a.mode == 0 && a.flat) {
         const int NT = W * a.tpl;
         const int64_t base = l0 * a.L;
-        for (int f = tid; f < nl * a.L; f += NT) store_io(out + base + f, load_io(in + base + f, nt), nt);
+        for (int f = tid; f < nl * a.L; f += NT) store_io(out + base + f, load_io(in + base + f, nt), nts);
         return;
     }
     int w, t;
@@ -80,7 +80,7 @@ __global__ void __launch_bounds__(MAXT) copy_pattern_kernel(CopyArgs a) {
     for (int s = 0; s < KMAX; ++s) {
         const int i = s % a.nb, r = s / a.nb;
         const int b = t + i * a.tpl;
-        if (r < a.r0 && b < B) store_io(out + base + (int64_t)(b + r * B) * stride, v[s], nt);
+        if (r < a.r0 && b < B) store_io(out + base + (int64_t)(b + r * B) * stride, v[s], nts);
     }
 }
 
@@ -115,7 +115,7 @@ int offt_copy_pass(offt_plan_t p, int i, const void* in, void* out, void* stream
     a.mode = pp.mode;
     a.flat = pp.mode == 0 && a.tpl < kDirectRowMinTpl;
     a.xcd_remap = pp.xcd;
-    a.stream_io = pp.stream;
+    a.stream_io = pp.stream | (pp.stream_src && in != out ? kStreamLoads : 0);
     const int64_t W = int64_t(1) << pp.logW;
     const int64_t nblocks = (a.nlines + W - 1) / W;
     const int threads = (int)(W * a.tpl);

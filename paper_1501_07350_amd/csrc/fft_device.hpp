@@ -610,6 +610,8 @@ template <int R, int... Rest> struct RadixProduct<R, Rest...> {
 };
 
 // ---- pass arguments --------------------------------------------------------
+constexpr int kStreamLoads = 1, kStreamStores = 2;   // PassArgs::stream_io
+
 struct PassArgs {
     const void* in;
     void* out;
@@ -630,7 +632,7 @@ struct PassArgs {
     int mode;           // 0: contiguous lines (M2 == 1), 1: strided lines,
                         // 2: rows in, strided lines out, 3: strided lines in, rows out
     int xcd_remap;      // 1: tiles in contiguous runs per XCD (xcd_tile)
-    int stream_io;      // 1: grid data loaded and stored with streaming (non-temporal) accesses
+    int stream_io;      // kStreamLoads | kStreamStores: grid data loaded / stored with streaming (non-temporal) accesses
     int conj_in;        // negate imaginary parts on load
     int conj_out;       // negate imaginary parts on store
     double scale;       // multiply on store
@@ -663,7 +665,8 @@ template <typename V, typename S> __device__ __forceinline__ V fix_out(V x, int 
 // lines are then not kept in the caches for reuse.  On MI355X that raises the
 // rate of the strided tile loads and stores of grids much larger than the
 // 256 MB Infinity Cache, and lowers it for grids that fit there, whose next
-// pass reads what the previous one left in the cache.
+// pass reads what the previous one left in the cache.  Between the two, only
+// the ends of a transform stream (set_edge_streams in planner.cpp).
 template <typename S> struct StreamVec { typedef S type __attribute__((vector_size(2 * sizeof(S)))); };
 template <typename V> __device__ __forceinline__ V load_stream(const V* p) {
     using S = decltype(V{}.x);
@@ -817,7 +820,7 @@ __device__ __forceinline__ void pass_tile_impl(const PassArgs& a, V* __restrict_
     const int cin = a.conj_in, cout = a.conj_out;
     const S scale = (S)a.scale;
     const bool active = tid < W * TPL;
-    const bool nt = !COHERENT && a.stream_io;
+    const bool nt = !COHERENT && (a.stream_io & kStreamLoads), nts = !COHERENT && (a.stream_io & kStreamStores);
     constexpr int R0 = FirstRadix<Rs...>::value;
     constexpr bool kTwiddles = sizeof...(Rs) > 1;
     const bool tw_first = !OVERLAP || a.nlines * (int64_t)(L * sizeof(V)) > kOverlapBytes;
@@ -839,7 +842,7 @@ __device__ __forceinline__ void pass_tile_impl(const PassArgs& a, V* __restrict_
         const int64_t M2 = a.M2;
         const V* g = in + base;
         V* go = out + base;
-        LineSink<V, COHERENT> sink{go, M2, ok, nt, cout, scale};
+        LineSink<V, COHERENT> sink{go, M2, ok, nts, cout, scale};
         StageRegs<V, L, TPL, R0> x;
         load_first_io<V, L, TPL, R0>(x, t, active, g, M2, nt);
         if constexpr (kTwiddles) twiddles_finish<V, L>(twl, tw0, tw1, tw, tid, tw_first);
@@ -858,7 +861,7 @@ __device__ __forceinline__ void pass_tile_impl(const PassArgs& a, V* __restrict_
             // (stores one by one: with the branch around all of them, as in
             // LineSink, pass c of 1024^3 complex64 took 2.75 ms instead of 2.69)
             auto sink = [&](int j, V x) {
-                if (ok) store_elem_io<COHERENT>(go + j, fix_out(x, cout, scale), nt);
+                if (ok) store_elem_io<COHERENT>(go + j, fix_out(x, cout, scale), nts);
             };
             StageRegs<V, L, TPL, R0> x;
             load_first_io<V, L, TPL, R0>(x, t, active, g, 1, nt);
@@ -903,7 +906,7 @@ __device__ __forceinline__ void pass_tile_impl(const PassArgs& a, V* __restrict_
                 if (active) {
                     for (int f = tid; f < nl * L; f += NT) {
                         const int lw = f / L, j = f - lw * L;
-                        store_elem_io<COHERENT>(go + f, fix_out(lds[lw * LP + lds_idx(j)], cout, scale), nt);
+                        store_elem_io<COHERENT>(go + f, fix_out(lds[lw * LP + lds_idx(j)], cout, scale), nts);
                     }
                 }
             } else {
@@ -912,7 +915,7 @@ __device__ __forceinline__ void pass_tile_impl(const PassArgs& a, V* __restrict_
                     const int f = tid + k * NT;
                     if (active && f < nl * L) {
                         const int lw = f / L, j = f - lw * L;
-                        store_io(go + f, fix_out(lds[lw * LP + lds_idx(j)], cout, scale), nt);
+                        store_io(go + f, fix_out(lds[lw * LP + lds_idx(j)], cout, scale), nts);
                     }
                 }
             }
@@ -981,7 +984,7 @@ __device__ __forceinline__ void pass_tile_transpose(const PassArgs& a, V* __rest
     const int cin = a.conj_in, cout = a.conj_out;
     const S scale = (S)a.scale;
     const bool active = tid < NT;
-    const bool nts = a.stream_io != 0;
+    const bool nt = a.stream_io & kStreamLoads, nts = a.stream_io & kStreamStores;
     const int64_t M2 = a.M2;
     constexpr int R0 = FirstRadix<Rs...>::value;
     // twiddles staged around the tile's first loads (pass_tile_impl)
@@ -1015,7 +1018,7 @@ __device__ __forceinline__ void pass_tile_transpose(const PassArgs& a, V* __rest
 #pragma unroll
             for (int k = 0; k < K; ++k) {
                 const int f = tid + k * NT;
-                if (active && f < nl * L) x[k] = load_io(in + rows[f / L] + f % L, nts);
+                if (active && f < nl * L) x[k] = load_io(in + rows[f / L] + f % L, nt);
             }
             if constexpr (kTwiddles) twiddles_finish<V, L>(twl, tw0, tw1, tw, tid, tw_first);
 #pragma unroll
@@ -1038,7 +1041,7 @@ __device__ __forceinline__ void pass_tile_transpose(const PassArgs& a, V* __rest
 #pragma unroll
                 for (int k = 0; k < K; ++k) {
                     const int f = tid + k * NT;
-                    if (active && f < nl * PART) x[k] = load_io(in + rows[f / PART] + p * PART + f % PART, nts);
+                    if (active && f < nl * PART) x[k] = load_io(in + rows[f / PART] + p * PART + f % PART, nt);
                 }
                 if (kTwiddles && p == 0) twiddles_finish<V, L>(twl, tw0, tw1, tw, tid, tw_first);
 #pragma unroll
@@ -1063,7 +1066,7 @@ __device__ __forceinline__ void pass_tile_transpose(const PassArgs& a, V* __rest
     } else {
         const V* g = in + base;
         StageRegs<V, L, TPL, R0> x;
-        load_first_io<V, L, TPL, R0>(x, t, active, g, M2, nts);
+        load_first_io<V, L, TPL, R0>(x, t, active, g, M2, nt);
         if constexpr (kTwiddles) twiddles_finish<V, L>(twl, tw0, tw1, tw, tid, tw_first);
         map_first<V, L, TPL, R0>(x, t, active, fix);
         if constexpr (P == 1) {

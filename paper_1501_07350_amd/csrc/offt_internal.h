@@ -73,6 +73,7 @@ struct PassPlan {
     int mode;                  // 0 contiguous lines, 1 strided lines, 2/3 transposing (PassArgs)
     int xcd = 0;               // tiles in contiguous runs per XCD (PassArgs::xcd_remap)
     int stream = 0;            // streaming loads and stores (PassArgs::stream_io)
+    int stream_src = 0;        // loads stream too in a launch out of place
     const void* tw;            // device twiddle table for L
     // Slab schedule (PlanChoice::slab): a pass over axis b or c after the
     // whole-grid pass over a runs on `slab` planes (Nb x Nc) at a time, every
@@ -138,9 +139,9 @@ int slab_start(const PassPlan* ps, int n);
 // kIoCached force one mode ("/s", "/c").
 enum { kIoAuto = 0, kIoStream = 1, kIoCached = 2 };
 constexpr int64_t kStreamMinBytes = int64_t(256) << 20;
-// Whether a pass over `bytes` of grid data streams under access mode io.
+// Access mode (PassArgs::stream_io) of a pass over `bytes` of grid data under io.
 inline int resolve_stream(int io, int64_t bytes) {
-    return io == kIoStream || (io == kIoAuto && bytes > kStreamMinBytes) ? 1 : 0;
+    return io == kIoStream || (io == kIoAuto && bytes > kStreamMinBytes) ? kStreamLoads | kStreamStores : 0;
 }
 
 // Plan choice for one grid shape, independent of device memory.

@@ -307,18 +307,23 @@ constexpr int64_t kTableMinLines = 256;
 // Size classes of kernel_defaults.txt.  The first line lies between the 4 MiB
 // and the 16 MiB timings: at 4 MiB the large grids' kernels of 128-point lines
 // (complex128) move 1.5 TB/s on strided lines where the narrow tiles move
-// 2.0, at 64 MiB 3.9 against 3.6.  The second: over boxes of 12 shapes the
-// second class's plans took 0.91, 0.96, 0.94 and 1.06 of the third's time at
-// 160, 208, 256 and 330 MiB of complex128, 0.93, 0.99, 1.00 and 1.26 of
-// complex64.
+// 2.0, at 64 MiB 3.9 against 3.6.  The second, where
+// the passes between begin to stream: at 205 to 256 MiB of complex64 (12
+// cubes, batched) the second class's plans took 0.94 of the third's time (216^3
+// x 3 228 against 254 us, 256^3 x 2 237 against 260, 144^3 x 9 202 against
+// 201), at 261 MiB 1.52; complex128, boxes of 12 shapes, 0.91, 0.96, 0.94 and
+// 1.06 at 160, 208, 256 and 330 MiB.  A complex64 plan with a transposing pass
+// also fills a workspace; three such plans run in turn took 254 us with the
+// third class and 272 with the second (256 x 320 x 384), one plan alone 238
+// and 228: its line lies at 192 MiB.
 constexpr int64_t kSmallGridBytes = int64_t(8) << 20;
-static int64_t large_grid_bytes(int dtype) { return int64_t(dtype == OFFT_C2C_F64 ? 256 : 192) << 20; }
+constexpr int64_t kLargeTransposedBytes = int64_t(192) << 20;
 
 // The measured default kernel and tile width of a pass over `lines` lines of
 // length L in a batch of grids of `bytes`; null where the table has none.
 static const KernelEntry* table_kernel(int dtype, int L, LineKind kind, int64_t lines, int64_t bytes, int* logW) {
     if (lines < kTableMinLines) return nullptr;
-    const int cls = bytes <= kSmallGridBytes ? 0 : (bytes <= large_grid_bytes(dtype) ? 1 : 2);
+    const int cls = bytes <= kSmallGridBytes ? 0 : (bytes <= kStreamMinBytes ? 1 : 2);
     for (const KernelDefault& d : kKernelDefaults) {
         if (d.dtype != dtype || d.kind != kind || d.L != L) continue;
         AxisSpec sp;
@@ -388,6 +393,10 @@ static const KernelEntry* default_kernel_transpose(int dtype, int L) {
 static void assign_default_kernels(PlanChoice& c, int dtype, const int64_t dims[3], int64_t batch,
                                    bool rules_only = false) {
     const int64_t points = dims[0] * dims[1] * dims[2] * batch;
+    int64_t bytes = points * (int64_t)elem_size(dtype);
+    for (int ax = 0; ax < 3; ++ax)
+        if (dims[ax] > 1 && axis_geom(c, ax) == kGeomTranspose && dtype == OFFT_C2C_F32 && bytes > kLargeTransposedBytes)
+            bytes = std::max(bytes, kStreamMinBytes + 1);
     for (int ax = 0; ax < 3; ++ax) {
         c.k[ax] = nullptr;
         c.logW[ax] = 0;
@@ -396,15 +405,14 @@ static void assign_default_kernels(PlanChoice& c, int dtype, const int64_t dims[
         const KernelEntry* k;
         int logW = 0;
         if (g == kGeomTranspose) {
-            k = table_kernel(dtype, (int)dims[ax], kTransposing, points / dims[ax], points * (int64_t)elem_size(dtype), &logW);
+            k = table_kernel(dtype, (int)dims[ax], kTransposing, points / dims[ax], bytes, &logW);
             if (!k) {
                 k = default_kernel_transpose(dtype, (int)dims[ax]);
                 logW = k ? fit_logW(k, 4, dtype, g) : 0;
             }
         } else {
             const bool strided = make_pass(dims, 1, ax, g, nullptr, 0).M2 > 1;
-            k = pass_kernel(dtype, (int)dims[ax], strided, rules_only ? 0 : points / dims[ax],
-                            points * (int64_t)elem_size(dtype), &logW);
+            k = pass_kernel(dtype, (int)dims[ax], strided, rules_only ? 0 : points / dims[ax], bytes, &logW);
         }
         if (k) {
             c.k[ax] = k;
@@ -870,6 +878,32 @@ static void set_slab(PassPlan* out, int n, int64_t planes, int64_t plane_elems, 
     }
 }
 
+// Streaming ends of a batch of grids whose passes are cached.  From half of
+// the Infinity Cache on, input and output do not both fit there, and the input
+// is not read again: out of place the first pass streams its loads.  The last
+// pass of a transposing plan reads one buffer and writes another, which no
+// pass reads: it streams its stores.  Measured on MI355X, before -> after:
+//   loads   256^3 complex128 258 -> 239 us, 300^3 complex64 255 -> 242,
+//           48 x 64^3 complex128 143 -> 128; in place 238 -> 257 (256^3), so
+//           a launch in place keeps its loads cached; 128 MiB, 256^3 complex64,
+//           three buffer pairs in turn 145 -> 126, one pair 123 -> 125; below,
+//           160^3 complex128 66.6 -> 70.8
+//   stores  reversed output order, 256 x 320 x 384 complex64 284 -> 249 us
+//           (with the loads 242), 192^3 complex128 115 -> 107, 128^3 36.6 -> 35.2
+constexpr int64_t kStreamSrcMinBytes = int64_t(128) << 20;
+constexpr int64_t kStreamDstMinBytes = int64_t(32) << 20;
+static void set_edge_streams(PassPlan* out, int n, int64_t bytes, const int* io) {
+    if (n < 2) return;
+    PassPlan &first = out[0], &last = out[n - 1];
+    if (bytes >= kStreamSrcMinBytes && bytes <= kStreamMinBytes && io[first.axis] == kIoAuto) first.stream_src = 1;
+    if (bytes >= kStreamDstMinBytes && last.mode >= 2 && io[last.axis] == kIoAuto) last.stream |= kStreamStores;
+}
+
+// Access mode of a launch of pass p.
+static int launch_streams(const PassPlan& p, const void* in, const void* out) {
+    return p.stream | (p.stream_src && in != out ? kStreamLoads : 0);
+}
+
 int build_passes_nd(const NdChoice& c, const int64_t* dims, int64_t batch, PassPlan* out) {
     int n = 0;
     for (int i = 0; i < c.ndim; ++i) {
@@ -879,6 +913,8 @@ int build_passes_nd(const NdChoice& c, const int64_t* dims, int64_t batch, PassP
     }
     if (c.slab > 0 && nd_slab_fits(c, dims))
         set_slab(out, n, batch * dims[0], dims[0] > 0 ? grid_elems_nd(c.ndim, dims) / dims[0] : 0, c.slab, c.io);
+    if (n > 0 && out[0].k)
+        set_edge_streams(out, n, grid_elems_nd(c.ndim, dims) * batch * (int64_t)elem_size(out[0].k->dtype), c.io);
     return n;
 }
 
@@ -901,6 +937,8 @@ int build_passes(const PlanChoice& c, const int64_t dims[3], int64_t batch, Pass
                                                                       (int64_t)elem_size(out[i].k->dtype));
         }
     }
+    if (n > 0 && out[0].k)
+        set_edge_streams(out, n, dims[0] * dims[1] * dims[2] * batch * (int64_t)elem_size(out[0].k->dtype), c.io);
     return n;
 }
 
@@ -950,7 +988,9 @@ static const KernelEntry* block_kernel_entry(int dtype, int64_t L) {
 //   one block per  8 x 100^3 complex64 65.8 -> 75.4 us (in the Infinity Cache),
 //   CU             64 of them 617 -> 549 us, 128^4 2.97 -> 2.80 ms (streaming);
 //                  128^3 alone 35.6 -> 27.3 us, 8 of them equal
-//   few blocks     12 x 150 x 60 complex64 14.3 -> 16.4 us
+//   few blocks     12 x 150 x 60 complex64 14.3 -> 16.4 us; a plane to a CU with
+//                  three-stage lines, 125^3 complex64 33.5 -> 36.2 us, but
+//                  250 x 125^2 44.7 -> 41.2 us
 static int fuse_rule(int dtype, int64_t A, int64_t B, int64_t C, int64_t grids) {
     if (C < 2 || B < 2 || !block_case_of_length(dtype, B) || !block_case_of_length(dtype, C)) return 0;
     const int64_t es = (int64_t)elem_size(dtype);
@@ -965,8 +1005,10 @@ static int fuse_rule(int dtype, int64_t A, int64_t B, int64_t C, int64_t grids) 
     }
     const int64_t lds = block_lds_elems(1, (int)B, (int)C) * es;
     if (lds > lds_limit()) return 0;
+    const bool two_stages = block_case_of_length(dtype, B)->nstages <= 2 && block_case_of_length(dtype, C)->nstages <= 2;
     if (lds <= kTwoPerCu ? (B * C <= 4096 || planes >= 64)
-                         : ((planes >= 64 && planes <= 256) || planes * B * C * es > kStreamMinBytes))
+                         : ((planes >= (two_stages ? 64 : 192) && planes <= 256) ||
+                            planes * B * C * es > kStreamMinBytes))
         return 2;
     return 0;
 }
@@ -1005,8 +1047,8 @@ hipError_t launch_block(const PassPlan* ps, const void* in, void* out, int conj_
     a.A = f == 3 ? ps[2].L : 1;
     a.pitch = block_pitch(a.C);
     a.rcp_C = block_rcp(a.C);
-    a.stream_in = ps[0].stream;
-    a.stream_out = ps[f - 1].stream;
+    a.stream_in = launch_streams(ps[0], in, out) & kStreamLoads;
+    a.stream_out = ps[f - 1].stream & kStreamStores;
     a.conj_in = conj_in;
     a.conj_out = conj_out;
     a.scale = scale;
@@ -1051,7 +1093,7 @@ hipError_t launch_pass(const PassPlan& p, const void* in, void* out, int conj_in
     a.logW = p.logW;
     a.mode = p.mode;
     a.xcd_remap = p.xcd;
-    a.stream_io = p.stream;
+    a.stream_io = launch_streams(p, in, out);
     a.conj_in = conj_in;
     a.conj_out = conj_out;
     a.scale = scale;

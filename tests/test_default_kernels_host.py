@@ -50,7 +50,7 @@ def test_default_plans_follow_the_size_classes(gk, prec):
     # rows longer than a block kernel's (256 points), so that every pass runs alone
     for shape in [(16, 20, 270), (32, 60, 288), (90, 100, 300), (128, 128, 320), (225, 320, 300), (512, 480, 450)]:
         n = shape[0] * shape[1] * shape[2]
-        limit = (256 if prec == "f64" else 192) << 20
+        limit = 256 << 20
         cls = 0 if n * es <= 8 << 20 else (1 if n * es <= limit else 2)
         f = _fields(offt.default_plan_string(shape, DTYPES[prec]))
         for i, ax in enumerate("abc"):
