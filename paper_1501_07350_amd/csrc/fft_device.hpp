@@ -873,11 +873,31 @@ __device__ __forceinline__ void pass_tile_impl(const PassArgs& a, V* __restrict_
             // all of a thread's loads in flight at once (f = tid + k NT, k < K)
             const int NT = W * TPL;
             constexpr int K = (L + TPL - 1) / TPL;
+            // The level kernels of uneven batches hold every case's code in one
+            // kernel, where K values held across the twiddles cost occupancy
+            // (93 registers for 63: 64 grids of complex64 735 us instead of
+            // 705): they take a few elements a thread at a time, 4 of complex64
+            // (706 -> 671 us; 8: 676) and 8 of complex128 (1632 -> 1317 us; 4:
+            // 1354), in the registers that they have.
+            constexpr int kLevelRows = sizeof(V) == 16 ? 8 : 4;
             const V* g = in + l0 * L;
             V* go = out + l0 * L;
             if constexpr (!OVERLAP) {
                 if (active) {
-                    for (int f = tid; f < nl * L; f += NT) {
+                    int f = tid;
+                    if constexpr (!COHERENT && !LOOPED) {
+                        for (; f + (kLevelRows - 1) * NT < nl * L; f += kLevelRows * NT) {
+                            V x[kLevelRows];
+#pragma unroll
+                            for (int u = 0; u < kLevelRows; ++u) x[u] = load_io(g + f + u * NT, nt);
+#pragma unroll
+                            for (int u = 0; u < kLevelRows; ++u) {
+                                const int fu = f + u * NT, lw = fu / L, j = fu - lw * L;
+                                lds[lw * LP + lds_idx(j)] = fix(x[u]);
+                            }
+                        }
+                    }
+                    for (; f < nl * L; f += NT) {
                         const int lw = f / L, j = f - lw * L;
                         lds[lw * LP + lds_idx(j)] = fix(load_elem<COHERENT>(g + f, nt));
                     }
@@ -904,7 +924,20 @@ __device__ __forceinline__ void pass_tile_impl(const PassArgs& a, V* __restrict_
             __syncthreads();
             if constexpr (!OVERLAP) {
                 if (active) {
-                    for (int f = tid; f < nl * L; f += NT) {
+                    int f = tid;
+                    if constexpr (!COHERENT && !LOOPED) {
+                        for (; f + (kLevelRows - 1) * NT < nl * L; f += kLevelRows * NT) {
+                            V x[kLevelRows];
+#pragma unroll
+                            for (int u = 0; u < kLevelRows; ++u) {
+                                const int fu = f + u * NT, lw = fu / L, j = fu - lw * L;
+                                x[u] = lds[lw * LP + lds_idx(j)];
+                            }
+#pragma unroll
+                            for (int u = 0; u < kLevelRows; ++u) store_io(go + f + u * NT, fix_out(x[u], cout, scale), nts);
+                        }
+                    }
+                    for (; f < nl * L; f += NT) {
                         const int lw = f / L, j = f - lw * L;
                         store_elem_io<COHERENT>(go + f, fix_out(lds[lw * LP + lds_idx(j)], cout, scale), nts);
                     }
