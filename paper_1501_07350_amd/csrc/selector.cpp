@@ -95,7 +95,7 @@ void plan_features(int dtype, const int64_t dims[3], int64_t batch, const PlanCh
         g[12] = (float)std::log2((double)k->nparts);
         g[13] = (float)c.xcd[ax];
         // the access mode the pass runs with (streaming or cached grid data)
-        g[14] = (float)resolve_stream(c.io[ax], (int64_t)(N * (double)batch) * (int64_t)elem_size(dtype));
+        g[14] = resolve_stream(c.io[ax], (int64_t)(N * (double)batch) * (int64_t)elem_size(dtype)) ? 1.f : 0.f;
     }
 }
 
