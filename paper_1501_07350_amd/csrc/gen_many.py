@@ -31,21 +31,14 @@ BATCH_LENGTHS = (48, 60, 64, 80, 96, 120, 128, 150, 160)
 CASE_SETS = {"batch": lambda L: L in BATCH_LENGTHS, "all": lambda L: L <= MANY_MAX_L}
 
 # Executors compiled into the library: (name, case set, persistent forms).
-# The "all" set (every length <= 160) has its level kernels only: its
-# work-queue kernel stopped responding on the GPU for a batch of mixed small
-# lengths although the same tile code and loop pass the CPU emulation
-# (tests/test_emu.py), so neither persistent form is built for it.  The level
-# kernels wait for nothing (kernel boundaries order the levels) and run the
-# stand-alone passes' tile code.
+# The "all" set (every length <= 160) has its level kernels only.
 EXECUTORS = (("batch", "batch", True), ("all", "all", False))
 
 
 def many_cases(prec, which="all", rules_only=False):
     """Kernel cases (L, radix sequence, threads per line) of one case set;
-    rules_only: without the kernels that only kernel_defaults.txt names,
-    which the executors do not compile (many-plans choose among the others;
-    with them the work-queue kernel of the batch set, which had twice the
-    cases then, did not come to an end on the GPU)."""
+    rules_only: without the kernels that only kernel_defaults.txt names, which
+    the executors do not compile (many-plans choose among the others)."""
     keep = CASE_SETS[which]
     return [e[:3] for e in entries(prec, parts=False) if keep(e[0]) and not (rules_only and not legacy(prec, *e))]
 
@@ -82,6 +75,30 @@ def _switch(fn, inline, tile, name, vt, cases):
     return out
 
 
+def _calls(name, vt, cases):
+    """The persistent kernel's dispatch: one out-of-line function per kernel
+    case and an inline switch that calls them.  (Inlined into the persistent
+    loop, loop-invariant code of every case would be hoisted and kept live
+    together.)  One function around the whole switch is not safe: beyond the
+    128 KiB that a conditional branch reaches the compiler adds branches
+    through s[30:31], where a function that calls nothing keeps its return
+    address unsaved; the return then jumps to the last such target and the
+    workgroup never ends (complex128, 15 cases: 157 KB; complex64: 125 KB with
+    15 cases, 184 KB with 25, 307 KB with 50).  A case's tile is 3 to 17 KB.
+    The case is uniform in the workgroup (readfirstlane: a scalar branch)."""
+    out = []
+    for i, (L, seq, tpl) in enumerate(cases):
+        rad = ", ".join(str(x) for x in seq)
+        out += [f"__device__ __noinline__ void tile_{name}_{i}(const PassArgs& a, {vt}* lds, int64_t l0) {{",
+                f"    pass_tile_coherent<{vt}, {L}, {tpl}, {rad}>(a, lds, l0);",
+                "}"]
+    out += [f"__device__ __forceinline__ void dispatch_{name}(int kid, const PassArgs& a, {vt}* lds, int64_t l0) {{",
+            "    switch (__builtin_amdgcn_readfirstlane(kid)) {"]
+    out += [f"        case {i}: tile_{name}_{i}(a, lds, l0); break;" for i in range(len(cases))]
+    out += ["        default: break;", "    }", "}"]
+    return out
+
+
 def _functor(struct, fn, name, vt):
     return [f"struct {struct}_{name} {{",
             f"    __device__ __forceinline__ void operator()(int kid, const PassArgs& a, {vt}* lds, int64_t l0) const {{",
@@ -98,10 +115,7 @@ def _executor_file(outdir, ex, persistent, prec, vt, dcode, cases):
              "namespace offt {",
              "namespace {"]
     if persistent:
-        # The whole switch is one out-of-line function called once per tile:
-        # inlined into the persistent loop, loop-invariant code of every case
-        # would be hoisted and kept live together.
-        lines += _switch("dispatch", "__noinline__", "pass_tile_coherent", name, vt, cases)
+        lines += _calls(name, vt, cases)
     # the level kernels are ordered by kernel boundaries: plain stores; one
     # tile per workgroup and no loop to hoist out of, so their dispatch is
     # inlined (no call frame)
