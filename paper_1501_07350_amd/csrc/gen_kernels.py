@@ -212,9 +212,11 @@ BLOCK_MAX_L = 256
 # A precision has two block kernels.  Lines of up to 100 points have radices up
 # to 10 and fit 80 registers in binary32 (six waves per SIMD) and 128 in
 # binary64; the longer lines' radices 12 to 16 take up to 128, and in binary64
-# more than 1024 threads leave.  (kernel, longest line, threads, attribute)
-BLOCK_KERNELS = {"f64": (("short", 100, 1024, ""), ("long", BLOCK_MAX_L, 512, "")),
-                 "f32": (("short", 100, 1024, "__attribute__((amdgpu_waves_per_eu(6))) "), ("long", BLOCK_MAX_L, 1024, ""))}
+# more than 1024 threads leave.  (kernel, longest line, threads, waves per SIMD
+# that its registers leave: 80, 128, 116 and 181 of them, attribute)
+BLOCK_KERNELS = {"f64": (("short", 100, 1024, 4, ""), ("long", BLOCK_MAX_L, 512, 2, "")),
+                 "f32": (("short", 100, 1024, 6, "__attribute__((amdgpu_waves_per_eu(6))) "),
+                         ("long", BLOCK_MAX_L, 1024, 4, ""))}
 # Radices of the block kernels' stages.
 BLOCK_RADICES = (2, 3, 4, 5, 6, 8, 9, 10, 12, 15, 16)
 
@@ -251,7 +253,7 @@ def emit_block(outdir):
     files, inc = [], []
     for prec, vt, dcode in (("f64", "double2", 0), ("f32", "float2", 1)):
         cases = block_cases(prec)
-        for name, max_l, threads, attr in BLOCK_KERNELS[prec]:
+        for name, max_l, threads, _, attr in BLOCK_KERNELS[prec]:
             lines = ["// generated by gen_kernels.py -- do not edit",
                      '#include "offt_internal.h"',
                      '#include "fft_block.hpp"',
@@ -287,11 +289,12 @@ def emit_block(outdir):
     for prec in BLOCK_KERNELS:
         for name, *_ in BLOCK_KERNELS[prec]:
             protos.append(f"hipError_t launch_block_{name}_{prec}(const BlockArgs& a, int64_t nblocks, int threads, size_t lds, hipStream_t s);")
-    protos.append("struct BlockKernel { int dtype; int max_l; int threads; hipError_t (*launch)(const BlockArgs&, int64_t, int, size_t, hipStream_t); };")
+    protos.append("struct BlockKernel { int dtype; int max_l; int threads; int waves; hipError_t (*launch)(const BlockArgs&, int64_t, int, size_t, hipStream_t); };")
+    protos.append(f"constexpr int kBlockMaxLine = {BLOCK_MAX_L};")
     protos.append("static const BlockKernel kBlockKernels[] = {")
     for prec, dcode in (("f64", 0), ("f32", 1)):
-        for name, max_l, threads, _ in BLOCK_KERNELS[prec]:
-            protos.append(f"    {{{dcode}, {max_l}, {threads}, &launch_block_{name}_{prec}}},")
+        for name, max_l, threads, waves, _ in BLOCK_KERNELS[prec]:
+            protos.append(f"    {{{dcode}, {max_l}, {threads}, {waves}, &launch_block_{name}_{prec}}},")
     protos.append("};")
     _write(os.path.join(outdir, "block_kernels.inc"), "\n".join(protos) + "\n")
     return files

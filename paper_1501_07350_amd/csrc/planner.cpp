@@ -951,6 +951,8 @@ static const BlockCase kBlockCases[] = {
 #include "_gen/block_cases.inc"
 };
 
+constexpr int64_t kCUs = 256, kCacheLine = 128;
+
 // Case of the block kernel for lines of kernel k's radix sequence, or -1 (the
 // index counts the cases of k's precision).
 static int block_case(const KernelEntry* k) {
@@ -974,6 +976,76 @@ static const KernelEntry* block_kernel_entry(int dtype, int64_t L) {
     for (const KernelEntry* k : kernels_for(dtype, (int)L))
         if (k->nparts == 1 && block_case(k) >= 0) return k;
     return nullptr;
+}
+
+// The block kernel of lines of up to `maxl` points.
+static const BlockKernel* block_kernel_for(int dtype, int maxl) {
+    for (const BlockKernel& bk : kBlockKernels)
+        if (bk.dtype == dtype && maxl <= bk.max_l) return &bk;
+    return nullptr;
+}
+
+// Threads of a workgroup that transforms one block of `blocks` (naxes of its
+// axes), and streams its stores or not; 0 without a kernel.
+//
+// Up to one block per CU: a thread for every line of the longest pass at once
+// (in threads per line).  Beyond that a CU holds several workgroups, as many as
+// its LDS and the kernel's waves per SIMD allow.  Of 64, 128, ... 1024 threads
+// (a workgroup's waves then spread evenly over the SIMDs; two lines at a time
+// at least) the most with which all blocks reside at once; if there are none,
+// the first that keeps the most threads resident.  Stores that stream pass L2
+// unmerged, so that there the lanes of a row of the last pass should span a
+// cache line.  The short kernels keep their earlier count, half of the lines at
+// once where two such workgroups still fill a CU (3072 planes of 48 x 48,
+// complex128: 112, 105, 94 and 85 us a transform with 576, 320, 384 and 192
+// threads), where all blocks reside with it or the other keeps less than a
+// fifth more threads.
+// Measured on 150 plane shapes per precision at 8, 24, 96 and 400 MiB (time
+// against the earlier count in every kernel): long lines 0.98, 0.82, 0.71 and
+// 0.81 in complex64, 0.92, 0.83, 0.79 and 0.84 in complex128; short ones 1.00,
+// 0.95, 0.93, 0.96 and 1.00, 0.94, 0.88, 0.89.  2013 planes of 50 x 125 in
+// complex64: 102 us with 1024 threads, 62 with 512 (separate passes 64).
+static int block_threads(int dtype, int A, int B, int C, int naxes, int64_t blocks, bool streamed,
+                         int64_t lds_max = lds_limit()) {
+    const BlockKernel* bk = block_kernel_for(dtype, std::max(std::max(A, B), C));
+    if (!bk) return 0;
+    const int64_t n = (int64_t)A * B * C, es = (int64_t)elem_size(dtype);
+    int64_t one = 0, least = 1, last = 1;
+    for (const int L : {C, B, A}) {
+        if (L < 2) continue;
+        const BlockCase* c = block_case_of_length(dtype, L);
+        if (!c) return 0;
+        one = std::max(one, n / L * c->tpl);
+        least = std::max<int64_t>(least, c->tpl);
+        last = c->tpl;
+    }
+    const auto waves = [](int64_t t) { return (t + 63) / 64 * 64; };
+    const auto in_kernel = [&](int64_t t) { return std::min<int64_t>(bk->threads, waves(std::max(t, least))); };
+    if (blocks <= kCUs) return (int)in_kernel(one);
+    const int64_t per_cu = lds_max / (block_lds_elems(A, B, C) * es), held = (blocks + kCUs - 1) / kCUs;
+    const int64_t slots = (int64_t)bk->waves * 4 * 64;
+    const auto groups = [&](int64_t t) { return std::min(per_cu, slots / t); };
+    const auto resident = [&](int64_t t) { return std::min(groups(t), held) * t; };
+    const int64_t row = naxes == 3 ? (int64_t)B * C : C;
+    const auto lines_of_cache = [&](int64_t t) { return !streamed || t / last >= row || t / last * es >= kCacheLine; };
+    const bool is_short = bk->max_l < kBlockMaxLine;
+    const int64_t earlier = in_kernel(per_cu * waves(one / 2) >= 1024 ? one / 2 : one);
+    if (is_short && groups(earlier) >= held) return (int)earlier;
+    int64_t best = 0, at_once = 0;
+    bool whole_rows = false;
+    for (int64_t t = 64; t <= bk->threads; t *= 2) {
+        if (t < least || (t < 2 * least && t < one && 2 * t <= bk->threads)) continue;
+        if (best && t / 2 >= one) break;
+        if (groups(t) >= held) at_once = t;
+        const bool ok = lines_of_cache(t);
+        if (!best || (ok && !whole_rows) || (ok == whole_rows && resident(t) > resident(best))) {
+            best = t;
+            whole_rows = ok;
+        }
+    }
+    if (at_once) return (int)at_once;
+    const bool keep = is_short && 5 * resident(best) < 6 * resident(earlier) && (lines_of_cache(earlier) || !whole_rows);
+    return (int)(keep ? earlier : best);
 }
 
 // Axes that run as one block kernel, by size: 3 (blocks are whole A x B x C
@@ -1035,12 +1107,10 @@ hipError_t launch_block(const PassPlan* ps, const void* in, void* out, int conj_
     a.in = in;
     a.out = out;
     a.naxes = f;
-    int tpl[3] = {1, 1, 1};
     for (int i = 0; i < f; ++i) {
         a.tw[i] = ps[i].tw;
         a.kid[i] = block_case(ps[i].k);
         if (a.kid[i] < 0) return hipErrorInvalidValue;
-        tpl[i] = block_case_of_length(ps[i].k->dtype, ps[i].L)->tpl;
     }
     a.C = ps[0].L;
     a.B = ps[1].L;
@@ -1054,26 +1124,12 @@ hipError_t launch_block(const PassPlan* ps, const void* in, void* out, int conj_
     a.scale = scale;
     const int64_t blocks = ps[f - 1].M1;
     const int dtype = ps[0].k->dtype;
-    const int64_t n = (int64_t)a.A * a.B * a.C;
     const int64_t lds = block_lds_elems(a.A, a.B, a.C) * (int64_t)elem_size(dtype);
     if (lds > lds_limit()) return hipErrorInvalidValue;
-    // Threads: enough for every line of a pass at once, or, where there are
-    // more blocks than CUs and 1024 threads still reside on a CU, half of that
-    // (two rounds of lines).  3072 planes of 48 x 48, complex128: 112, 105, 94
-    // and 85 us a transform with 576, 320, 384 (one round) and 192 threads;
-    // 4096 planes of 64 x 64, two to a CU: 192 and 204 us with 512 and 256.
-    const int64_t one = std::max(std::max(n / a.C * tpl[0], n / a.B * tpl[1]), f == 3 ? n / a.A * tpl[2] : 0);
-    const int64_t per_cu = lds_limit() / lds;
-    int64_t want = one;
-    if (blocks > 256 && per_cu * ((one / 2 + 63) / 64 * 64) >= 1024) want = one / 2;
-    const int maxl = std::max(std::max(a.A, a.B), a.C);
-    for (const BlockKernel& bk : kBlockKernels) {
-        if (bk.dtype != dtype || maxl > bk.max_l) continue;
-        const int64_t least = std::max(std::max(tpl[0], tpl[1]), tpl[2]);
-        const int threads = (int)std::min<int64_t>(bk.threads, (std::max(want, least) + 63) / 64 * 64);
-        return bk.launch(a, blocks, threads, (size_t)lds, s);
-    }
-    return hipErrorInvalidValue;
+    const int threads = block_threads(dtype, a.A, a.B, a.C, f, blocks, a.stream_out != 0);
+    const BlockKernel* bk = block_kernel_for(dtype, std::max(std::max(a.A, a.B), a.C));
+    if (threads < 1 || blocks > int64_t(0xffffffffu) / threads) return hipErrorInvalidValue;
+    return bk->launch(a, blocks, threads, (size_t)lds, s);
 }
 
 hipError_t launch_pass(const PassPlan& p, const void* in, void* out, int conj_in, int conj_out,
@@ -1115,3 +1171,15 @@ hipError_t launch_pass(const PassPlan& p, const void* in, void* out, int conj_in
 }
 
 }  // namespace offt
+
+using namespace offt;
+
+extern "C" {
+
+// Not part of the C ABI: the threads of a block launch for a device with
+// lds_max bytes of LDS per workgroup (tests).
+int offt_test_block_threads(int dtype, int64_t A, int64_t B, int64_t C, int64_t blocks, int streamed, int64_t lds_max) {
+    return block_threads(dtype, (int)A, (int)B, (int)C, A > 1 ? 3 : 2, blocks, streamed != 0, lds_max);
+}
+
+}  // extern "C"
