@@ -423,7 +423,7 @@ static void assign_default_kernels(PlanChoice& c, int dtype, const int64_t dims[
     }
 }
 
-static int fuse_rule(int dtype, int64_t A, int64_t B, int64_t C, int64_t grids);
+static int fuse_rule(int dtype, int64_t A, int64_t B, int64_t C, int64_t grids, int64_t lds_max = lds_limit());
 static const KernelEntry* block_kernel_entry(int dtype, int64_t L);
 
 // The last axes of a default plan that run as a block kernel take kernels of
@@ -1059,29 +1059,57 @@ static int block_threads(int dtype, int A, int B, int C, int naxes, int64_t bloc
 //                  64 x 32^3 complex128 37.7 -> 29.5 us
 //   one block per  8 x 100^3 complex64 65.8 -> 75.4 us (in the Infinity Cache),
 //   CU             64 of them 617 -> 549 us, 128^4 2.97 -> 2.80 ms (streaming);
-//                  128^3 alone 35.6 -> 27.3 us, 8 of them equal
+//                  128^3 alone 35.6 -> 27.3 us, 8 of them equal; 65 to 113
+//                  planes of 36 to 100 x 72 to 240: 0.72 to 0.98 of the
+//                  separate passes' speed
 //   few blocks     12 x 150 x 60 complex64 14.3 -> 16.4 us; a plane to a CU with
 //                  three-stage lines, 125^3 complex64 33.5 -> 36.2 us, but
 //                  250 x 125^2 44.7 -> 41.2 us
-static int fuse_rule(int dtype, int64_t A, int64_t B, int64_t C, int64_t grids) {
+//   tiny blocks    each costs a workgroup, 0.4 to 0.8 ns: 8192 planes of 2^2 to
+//                  12^2 points 8 to 12 us against 10 to 14, 9715 of 30 x 6 in
+//                  complex64 20 -> 13, 65536 of 2^2, 8^2 and 16^2 9.8 -> 39,
+//                  24 -> 52 and 82 -> 75 (streaming: 331200 of 20 x 5 in
+//                  complex128 636 -> 400); 32768 grids of 3^3, 4^3 and 5^3 in
+//                  complex64 15 -> 28, 31 -> 30, 39 -> 34
+//   three stages   along b, above 64 MiB: 6742 planes of 243 x 32 complex64 301
+//                  -> 586 us, 30340 of 216 x 8 345 -> 398, 8738 of 200 x 15
+//                  complex128 359 -> 439; along c they gain (3145 planes of 36 x
+//                  250 complex64 291 -> 221)
+static int fuse_rule(int dtype, int64_t A, int64_t B, int64_t C, int64_t grids, int64_t lds_max) {
     if (C < 2 || B < 2 || !block_case_of_length(dtype, B) || !block_case_of_length(dtype, C)) return 0;
     const int64_t es = (int64_t)elem_size(dtype);
     constexpr int64_t kTwoPerCu = 80 * 1024;
+    // the most blocks by their bytes (any number from `large` on)
+    const auto few = [](int64_t bytes, int64_t blocks, int64_t large) {
+        return bytes >= large || blocks <= (bytes < 1000 ? 8192 : 16384);
+    };
     const int64_t planes = A * grids;
     // up to 64 rows the contiguous pass keeps the rules' kernels, radix 16 in
     // complex128 and up to 8 in complex64
     if (planes * B <= 64) return 0;
+    const bool streamed = planes * B * C * es > kStreamMinBytes;
+    // a launch holds at most 2^32 - 1 threads
+    const auto launches = [&](int64_t a, int naxes, int64_t blocks) {
+        for (const bool st : {false, true}) {
+            const int t = block_threads(dtype, (int)a, (int)B, (int)C, naxes, blocks, st, lds_max);
+            if (t < 1 || blocks > int64_t(0xffffffffu) / t) return false;
+        }
+        return true;
+    };
     if (A > 1 && block_case_of_length(dtype, A)) {
         const int64_t lds = block_lds_elems((int)A, (int)B, (int)C) * es;
-        if (lds <= lds_limit() && (grids >= 512 || (lds <= kTwoPerCu && A * B * C <= 4096))) return 3;
+        if (lds <= lds_max && (grids >= 512 || (lds <= kTwoPerCu && A * B * C <= 4096)) &&
+            few(A * B * C * es, grids, 1100) && launches(A, 3, grids))
+            return 3;
     }
     const int64_t lds = block_lds_elems(1, (int)B, (int)C) * es;
-    if (lds > lds_limit()) return 0;
-    const bool two_stages = block_case_of_length(dtype, B)->nstages <= 2 && block_case_of_length(dtype, C)->nstages <= 2;
+    if (lds > lds_max) return 0;
+    if (!few(B * C * es, planes, streamed ? 100 * es : 2048)) return 0;
+    const int sb = block_case_of_length(dtype, B)->nstages, sc = block_case_of_length(dtype, C)->nstages;
+    if (sb > 2 && planes * B * C * es > (int64_t(64) << 20)) return 0;
     if (lds <= kTwoPerCu ? (B * C <= 4096 || planes >= 64)
-                         : ((planes >= (two_stages ? 64 : 192) && planes <= 256) ||
-                            planes * B * C * es > kStreamMinBytes))
-        return 2;
+                         : ((planes >= (std::max(sb, sc) <= 2 ? 128 : 192) && planes <= kCUs) || streamed))
+        return launches(1, 2, planes) ? 2 : 0;
     return 0;
 }
 
@@ -1176,8 +1204,12 @@ using namespace offt;
 
 extern "C" {
 
-// Not part of the C ABI: the threads of a block launch for a device with
-// lds_max bytes of LDS per workgroup (tests).
+// Not part of the C ABI: the block rule and the threads of a block launch for
+// a device with lds_max bytes of LDS per workgroup (tests).
+int offt_test_fuse_rule(int dtype, int64_t A, int64_t B, int64_t C, int64_t grids, int64_t lds_max) {
+    return fuse_rule(dtype, A, B, C, grids, lds_max);
+}
+
 int offt_test_block_threads(int dtype, int64_t A, int64_t B, int64_t C, int64_t blocks, int streamed, int64_t lds_max) {
     return block_threads(dtype, (int)A, (int)B, (int)C, A > 1 ? 3 : 2, blocks, streamed != 0, lds_max);
 }
