@@ -319,11 +319,19 @@ constexpr int64_t kTableMinLines = 256;
 constexpr int64_t kSmallGridBytes = int64_t(8) << 20;
 constexpr int64_t kLargeTransposedBytes = int64_t(192) << 20;
 
+// Streaming strided lines: strides below a cache line do not follow the table
+// (kernel_defaults.txt says what was measured).
+constexpr int64_t kCacheLine = 128;
+
 // The measured default kernel and tile width of a pass over `lines` lines of
-// length L in a batch of grids of `bytes`; null where the table has none.
-static const KernelEntry* table_kernel(int dtype, int L, LineKind kind, int64_t lines, int64_t bytes, int* logW) {
+// length L and element stride m2 in a batch of grids of `bytes`; null where the
+// table has none.
+static const KernelEntry* table_kernel(int dtype, int L, LineKind kind, int64_t m2, int64_t lines, int64_t bytes,
+                                       int* logW) {
     if (lines < kTableMinLines) return nullptr;
     const int cls = bytes <= kSmallGridBytes ? 0 : (bytes <= kStreamMinBytes ? 1 : 2);
+    const int64_t row = m2 * (int64_t)elem_size(dtype);
+    if (cls == 2 && kind == kStrided && row < (L < 512 ? kCacheLine : kCacheLine / 4)) return nullptr;
     for (const KernelDefault& d : kKernelDefaults) {
         if (d.dtype != dtype || d.kind != kind || d.L != L) continue;
         AxisSpec sp;
@@ -336,8 +344,9 @@ static const KernelEntry* table_kernel(int dtype, int L, LineKind kind, int64_t 
 
 // The kernel and width of a pass that does not transpose: the table's, or
 // the rules' where it has none.
-static const KernelEntry* pass_kernel(int dtype, int L, bool strided, int64_t lines, int64_t bytes, int* logW) {
-    if (const KernelEntry* k = table_kernel(dtype, L, strided ? kStrided : kContiguous, lines, bytes, logW)) return k;
+static const KernelEntry* pass_kernel(int dtype, int L, int64_t m2, int64_t lines, int64_t bytes, int* logW) {
+    const bool strided = m2 > 1;
+    if (const KernelEntry* k = table_kernel(dtype, L, strided ? kStrided : kContiguous, m2, lines, bytes, logW)) return k;
     const KernelEntry* k = default_kernel(dtype, L, strided);
     *logW = default_logW(k, dtype, strided);
     return k;
@@ -405,14 +414,14 @@ static void assign_default_kernels(PlanChoice& c, int dtype, const int64_t dims[
         const KernelEntry* k;
         int logW = 0;
         if (g == kGeomTranspose) {
-            k = table_kernel(dtype, (int)dims[ax], kTransposing, points / dims[ax], bytes, &logW);
+            k = table_kernel(dtype, (int)dims[ax], kTransposing, 1, points / dims[ax], bytes, &logW);
             if (!k) {
                 k = default_kernel_transpose(dtype, (int)dims[ax]);
                 logW = k ? fit_logW(k, 4, dtype, g) : 0;
             }
         } else {
-            const bool strided = make_pass(dims, 1, ax, g, nullptr, 0).M2 > 1;
-            k = pass_kernel(dtype, (int)dims[ax], strided, rules_only ? 0 : points / dims[ax], bytes, &logW);
+            const int64_t m2 = make_pass(dims, 1, ax, g, nullptr, 0).M2;
+            k = pass_kernel(dtype, (int)dims[ax], m2, rules_only ? 0 : points / dims[ax], bytes, &logW);
         }
         if (k) {
             c.k[ax] = k;
@@ -455,7 +464,7 @@ PassPlan contiguous_pass(int dtype, int L, int64_t lines, int64_t grid_bytes) {
     p.mode = 0;
     p.xcd = 0;
     p.tw = nullptr;
-    p.k = pass_kernel(dtype, L, false, lines, grid_bytes, &p.logW);
+    p.k = pass_kernel(dtype, L, 1, lines, grid_bytes, &p.logW);
     p.stream = resolve_stream(kIoAuto, grid_bytes);
     return p;
 }
@@ -779,9 +788,10 @@ NdChoice default_choice_nd(int dtype, int ndim, const int64_t* dims, int64_t bat
         c.k[ax] = nullptr;
         c.logW[ax] = 0;
         if (dims[ax] <= 1) continue;
-        const bool strided = make_pass_nd(ndim, dims, 1, ax, nullptr, 0).M2 > 1;
+        const int64_t m2 = make_pass_nd(ndim, dims, 1, ax, nullptr, 0).M2;
+        const bool strided = m2 > 1;
         int logW = 0;
-        const KernelEntry* k = pass_kernel(dtype, (int)dims[ax], strided, points / dims[ax],
+        const KernelEntry* k = pass_kernel(dtype, (int)dims[ax], m2, points / dims[ax],
                                            points * (int64_t)elem_size(dtype), &logW);
         if (k) {
             c.k[ax] = k;
@@ -951,7 +961,7 @@ static const BlockCase kBlockCases[] = {
 #include "_gen/block_cases.inc"
 };
 
-constexpr int64_t kCUs = 256, kCacheLine = 128;
+constexpr int64_t kCUs = 256;
 
 // Case of the block kernel for lines of kernel k's radix sequence, or -1 (the
 // index counts the cases of k's precision).
