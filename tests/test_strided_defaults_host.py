@@ -1,0 +1,36 @@
+"""Default kernels of streaming strided passes by the stride, host side."""
+import importlib.util
+import os
+
+import pytest
+import torch
+
+import paper_1501_07350_amd as offt
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_1501_07350_amd", "csrc")
+DTYPES = {"f64": torch.complex128, "f32": torch.complex64}
+
+
+@pytest.fixture(scope="module")
+def gk():
+    spec = importlib.util.spec_from_file_location("gen_kernels_strided", os.path.join(CSRC, "gen_kernels.py"))
+    mod = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(mod)
+    return mod
+
+
+def _fields(plan):
+    return dict(f.split("=", 1) for f in plan.split(";"))
+
+
+@pytest.mark.parametrize("prec,stride,from_table", [("f64", 5, False), ("f64", 6, False), ("f64", 8, True), ("f32", 5, False),
+                                                    ("f32", 15, False), ("f32", 16, True)])
+def test_strides_below_a_cache_line(gk, prec, stride, from_table):
+    """Axis c of a 4-D grid above 256 MiB, 300 points on a stride of `stride`
+    elements: from 128 bytes on the table's kernel, below one of the rules."""
+    shape = (90, 400, 300, stride)
+    plan = offt.plan_string_nd(shape, DTYPES[prec])
+    seq, tpl, P = gk.parse_spec(300, _fields(plan)["c"].replace("/x", ""))
+    table = {(p, k, L): specs for p, k, L, specs in gk.default_lines()}[(prec, "s", 300)]
+    assert ((seq, tpl, P) == gk.parse_spec(300, table[2])) == from_table
+    assert from_table or gk.legacy(prec, 300, seq, tpl, P)
