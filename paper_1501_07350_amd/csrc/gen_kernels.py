@@ -147,12 +147,21 @@ def parse_spec(L, spec):
 
 
 @functools.lru_cache(maxsize=None)
+def _default_rows():
+    with open(DEFAULTS) as f:
+        return tuple(tuple(ln.split()) for ln in f if ln.strip() and not ln.startswith("#"))
+
+
+@functools.lru_cache(maxsize=None)
 def default_lines():
     """(precision, line kind, length, specs) of every line of
-    kernel_defaults.txt."""
-    with open(DEFAULTS) as f:
-        rows = [ln.split() for ln in f if ln.strip() and not ln.startswith("#")]
-    return tuple((r[0], r[1], int(r[2]), tuple(r[3:])) for r in rows)
+    kernel_defaults.txt that names kernels."""
+    return tuple((r[0], r[1], int(r[2]), tuple(r[3:])) for r in _default_rows() if r[0] != "half")
+
+
+def half_lengths(prec):
+    """Lengths whose strided lines take half of the width on aligned rows."""
+    return {int(n) for r in _default_rows() if r[:2] == ("half", prec) for n in r[2:]}
 
 
 def default_entries(prec, L):
@@ -307,15 +316,18 @@ def _write(path, text):
 
 
 def emit_defaults(outdir):
-    """kernel_defaults.inc: {dtype, line kind, L, {spec per size class}} rows."""
+    """kernel_defaults.inc: {dtype, line kind, L, {spec per size class}, half
+    of the last width on aligned rows} rows."""
     rows = []
     for prec, kind, L, specs in default_lines():
         for s in specs:
             seq, tpl, P = parse_spec(L, s)
             assert len(specs) == 3 and (P == 1 or (kind != "c" and splits(L, seq, P))), (prec, kind, L, s)
             assert kind != "t" or transposes(seq, P), (prec, kind, L, s)
+        half = kind == "s" and L in half_lengths(prec)
+        assert not half or int(specs[2].split("/")[1]) > 1
         rows.append(f"    {{{0 if prec == 'f64' else 1}, {'cst'.index(kind)}, {L}, "
-                    f"{{{', '.join(chr(34) + s + chr(34) for s in specs)}}}}},")
+                    f"{{{', '.join(chr(34) + s + chr(34) for s in specs)}}}, {int(half)}}},")
     text = "\n".join(rows) + "\n"
     _write(os.path.join(outdir, "kernel_defaults.inc"), text)
 

@@ -284,6 +284,7 @@ struct KernelDefault {
     int kind;              // LineKind
     int L;
     const char* spec[3];
+    int half;              // strided lines: half of the last spec's width on aligned rows
 };
 const KernelDefault kKernelDefaults[] = {
 #include "_gen/kernel_defaults.inc"
@@ -319,8 +320,9 @@ constexpr int64_t kTableMinLines = 256;
 constexpr int64_t kSmallGridBytes = int64_t(8) << 20;
 constexpr int64_t kLargeTransposedBytes = int64_t(192) << 20;
 
-// Streaming strided lines: strides below a cache line do not follow the table
-// (kernel_defaults.txt says what was measured).
+// Streaming strided lines: rows of whole cache lines may take narrower tiles,
+// strides below a cache line do not follow the table (kernel_defaults.txt says
+// what was measured).
 constexpr int64_t kCacheLine = 128;
 
 // The measured default kernel and tile width of a pass over `lines` lines of
@@ -336,7 +338,9 @@ static const KernelEntry* table_kernel(int dtype, int L, LineKind kind, int64_t 
         if (d.dtype != dtype || d.kind != kind || d.L != L) continue;
         AxisSpec sp;
         const KernelEntry* k = parse_axis_spec(d.spec[cls], &sp) ? find_kernel(dtype, L, sp) : nullptr;
-        if (k) *logW = fit_logW(k, ilog2(sp.W), dtype, kind == kTransposing ? kGeomTranspose : kGeomNatural);
+        if (!k) return nullptr;
+        if (cls == 2 && d.half && (row % kCacheLine == 0 || row < kCacheLine)) sp.W /= 2;
+        *logW = fit_logW(k, ilog2(sp.W), dtype, kind == kTransposing ? kGeomTranspose : kGeomNatural);
         return k;
     }
     return nullptr;

@@ -34,3 +34,16 @@ def test_strides_below_a_cache_line(gk, prec, stride, from_table):
     table = {(p, k, L): specs for p, k, L, specs in gk.default_lines()}[(prec, "s", 300)]
     assert ((seq, tpl, P) == gk.parse_spec(300, table[2])) == from_table
     assert from_table or gk.legacy(prec, 300, seq, tpl, P)
+
+
+@pytest.mark.parametrize("L,listed", [(75, True), (125, True), (80, False), (100, False)])
+@pytest.mark.parametrize("columns", [500, 512, 540, 640])
+def test_width_by_row_alignment(gk, L, listed, columns):
+    """Streaming strided lines of a length in the half list: the table's width
+    where rows are no whole cache lines, half of it where they are; other
+    lengths keep the width.  (Lengths whose tiles fit any device's LDS.)"""
+    assert (L in gk.half_lengths("f32")) == listed
+    spec = {(p, k, n): s for p, k, n, s in gk.default_lines()}[("f32", "s", L)][2].split("/")
+    got = _fields(offt.default_plan_string((1000, L, columns), DTYPES["f32"]))["b"].split("/")
+    assert got[0] == spec[0]
+    assert int(got[1]) == int(spec[1]) // (2 if listed and columns * 8 % 128 == 0 else 1)
