@@ -283,8 +283,8 @@ def emit_block(outdir):
                       "}  // namespace",
                       f"hipError_t launch_block_{name}_{prec}(const BlockArgs& a, int64_t nblocks, int threads, size_t lds, "
                       "hipStream_t s) {",
-                      "    static std::atomic<size_t> lds_set{65536};",
-                      f"    return launch_block_kernel(&fft_block_{name}_{prec}, lds_set, a, nblocks, threads, lds, s);",
+                      "    static std::atomic<uint64_t> lds_raised{0};",
+                      f"    return launch_kernel(&fft_block_{name}_{prec}, lds_raised, a, nblocks, threads, lds, s);",
                       "}",
                       "}  // namespace offt"]
             path = os.path.join(outdir, f"block_{name}_{prec}.hip")
@@ -351,26 +351,14 @@ def emit(outdir):
                 "template <int MAXT, int L, int TPL, int P, int... Rs>",
                 "hipError_t launch_one(const PassArgs& a, int64_t nblocks, int threads, size_t lds, hipStream_t s) {",
                 f"    auto* k = &fft_pass_kernel<{vt}, MAXT, L, TPL, P, Rs...>;",
-                "    static size_t lds_set = 65536;",
-                "    if (lds > lds_set) {",
-                "        hipError_t e = hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);",
-                "        if (e != hipSuccess) return e;",
-                "        lds_set = lds;",
-                "    }",
-                "    hipLaunchKernelGGL(k, dim3((unsigned)nblocks), dim3(threads), lds, s, a);",
-                "    return hipGetLastError();",
+                "    static std::atomic<uint64_t> lds_raised{0};",
+                "    return launch_kernel(k, lds_raised, a, nblocks, threads, lds, s);",
                 "}",
                 "template <int L, int TPL, int P, int... Rs>",
                 "hipError_t launch_t_one(const PassArgs& a, int64_t nblocks, int threads, size_t lds, hipStream_t s) {",
                 f"    auto* k = &fft_tpass_kernel<{vt}, {TRANSPOSE_MAX_THREADS}, L, TPL, P, Rs...>;",
-                "    static size_t lds_set = 65536;",
-                "    if (lds > lds_set) {",
-                "        hipError_t e = hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);",
-                "        if (e != hipSuccess) return e;",
-                "        lds_set = lds;",
-                "    }",
-                "    hipLaunchKernelGGL(k, dim3((unsigned)nblocks), dim3(threads), lds, s, a);",
-                "    return hipGetLastError();",
+                "    static std::atomic<uint64_t> lds_raised{0};",
+                "    return launch_kernel(k, lds_raised, a, nblocks, threads, lds, s);",
                 "}",
                 "}  // namespace",
                 f"extern KernelEntry g_{name}[];",

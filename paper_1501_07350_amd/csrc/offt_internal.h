@@ -10,6 +10,7 @@
 
 #include "fft_block.hpp"
 #include "fft_device.hpp"
+#include "lds_attr.hpp"
 
 namespace offt {
 
@@ -111,14 +112,18 @@ void set_fuse(PassPlan* ps, int n);
 // Launches passes ps[0..ps[0].fuse) as one block kernel.
 hipError_t launch_block(const PassPlan* ps, const void* in, void* out, int conj_in, int conj_out, double scale,
                         hipStream_t s);
-template <typename K>
-hipError_t launch_block_kernel(K* k, std::atomic<size_t>& lds_set, const BlockArgs& a, int64_t nblocks, int threads,
-                               size_t lds, hipStream_t s) {
-    // lds_set: the kernel's dynamic LDS limit so far (64 KiB until raised)
-    if (lds > lds_set.load()) {
-        const hipError_t e = hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+// Launches kernel k; `done`: the devices on which its LDS limit is raised.
+template <typename K, typename Args>
+hipError_t launch_kernel(K* k, std::atomic<uint64_t>& done, const Args& a, int64_t nblocks, int threads, size_t lds,
+                         hipStream_t s) {
+    if (lds > kDefaultLds) {
+        int dev = 0;
+        hipError_t e = hipGetDevice(&dev);
         if (e != hipSuccess) return e;
-        lds_set.store(lds);
+        e = (hipError_t)raise_lds_limit(done, dev, lds, (size_t)lds_limit(), [&](size_t limit) {
+            return (int)hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)limit);
+        });
+        if (e != hipSuccess) return e;
     }
     hipLaunchKernelGGL(k, dim3((unsigned)nblocks), dim3(threads), lds, s, a);
     return hipGetLastError();
