@@ -497,9 +497,9 @@ PlanChoice default_choice_reversed(int dtype, const int64_t dims[3], int64_t bat
     return c;
 }
 
-std::vector<PlanChoice> candidate_choices(int dtype, const int64_t dims[3]) {
+std::vector<PlanChoice> candidate_choices(int dtype, const int64_t dims[3], int64_t batch, bool rules_only) {
     std::vector<PlanChoice> out;
-    const PlanChoice base = default_choice(dtype, dims);
+    const PlanChoice base = default_choice(dtype, dims, batch, rules_only);
     out.push_back(base);
     // per-axis variants with the default order: other kernels (radix
     // sequence, threads per line, exchange parts on strided axes) and tile

@@ -30,8 +30,8 @@ namespace offt {
 
 static const int kOrders[6][3] = {{2, 1, 0}, {2, 0, 1}, {1, 2, 0}, {1, 0, 2}, {0, 2, 1}, {0, 1, 2}};
 
-std::vector<PlanChoice> selector_candidates(int dtype, const int64_t dims[3], int64_t batch) {
-    std::vector<PlanChoice> out = candidate_choices(dtype, dims);
+std::vector<PlanChoice> selector_candidates(int dtype, const int64_t dims[3], int64_t batch, bool rules_only) {
+    std::vector<PlanChoice> out = candidate_choices(dtype, dims, batch, rules_only);
     if (out.empty()) return out;
     // the heuristic with one axis's access mode switched (streaming <->
     // cached grid data; by default the mode follows the grid's size)
@@ -161,7 +161,7 @@ static float forward(const Weights& w, const float* x) {
 }
 
 int learned_choice(int dtype, const int64_t dims[3], int64_t batch, const char* weights_path, PlanChoice* c,
-                   std::string* why) {
+                   std::string* why, bool rules_only) {
     if (!weights_path) { *why = "no weights"; return OFFT_ERR_IO; }
     static std::mutex mu;
     static std::map<std::string, Weights> cache;
@@ -175,7 +175,7 @@ int learned_choice(int dtype, const int64_t dims[3], int64_t batch, const char* 
         }
         w = it->second;
     }
-    const std::vector<PlanChoice> cands = selector_candidates(dtype, dims, batch);
+    const std::vector<PlanChoice> cands = selector_candidates(dtype, dims, batch, rules_only);
     if (cands.empty()) { *why = "no candidate plans"; return OFFT_ERR_UNSUPPORTED_SIZE; }
     std::vector<float> x(kFeatureDim);
     int best = -1;

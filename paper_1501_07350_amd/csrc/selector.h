@@ -25,7 +25,8 @@ void plan_features(int dtype, const int64_t dims[3], int64_t batch, const PlanCh
 // the predicted-fastest one.  Fails (non-zero, reason in *why) when the weights
 // are missing or unreadable or do not match the feature layout; the caller
 // then falls back to exhaustive timing.
+// rules_only: among the kernels of the radix-sequence rules (default_choice).
 int learned_choice(int dtype, const int64_t dims[3], int64_t batch, const char* weights_path,
-                   PlanChoice* c, std::string* why);
+                   PlanChoice* c, std::string* why, bool rules_only = false);
 
 }  // namespace offt

@@ -548,7 +548,7 @@ int select_plan(offt_plan_s* p, const offt_opts& o, PlanChoice* choice, PlanChoi
     }
     if (o.tune == OFFT_TUNE_LEARNED) {
         std::string why;
-        if (learned_choice(p->dtype, p->dims, p->batch, o.weights_path, choice, &why) == OFFT_SUCCESS) {
+        if (learned_choice(p->dtype, p->dims, p->batch, o.weights_path, choice, &why, p->rules_only) == OFFT_SUCCESS) {
             p->tune_log = "learned";
             return OFFT_SUCCESS;
         }
@@ -838,6 +838,7 @@ extern "C" int offt_tune_table(int64_t Na, int64_t Nb, int64_t Nc, int dtype, in
     tmp.dtype = dtype;
     tmp.dims[0] = Na; tmp.dims[1] = Nb; tmp.dims[2] = Nc;
     tmp.batch = batch;
+    tmp.allow_fuse = true;   // as a plan runs them
     hipStream_t s = static_cast<hipStream_t>(stream);
     const std::vector<PlanChoice> cands = selector_candidates(dtype, tmp.dims, batch);
     for (int i = 0; i < std::min((int)cands.size(), max) && rc == OFFT_SUCCESS; ++i)
