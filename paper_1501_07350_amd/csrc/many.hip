@@ -515,8 +515,7 @@ static int choose_many(offt_plan_s* p, const offt_opts& o) {
         const auto key = std::make_tuple(G.dims[0], G.dims[1], G.dims[2]);
         auto it = chosen.find(key);
         if (it == chosen.end()) {
-            const PlanChoice rules = default_choice(p->dtype, G.dims, 1, true);
-            PlanChoice c = rules;
+            PlanChoice c = default_choice(p->dtype, G.dims, 1, true);
             if (o.tune == OFFT_TUNE_EXHAUSTIVE || o.tune == OFFT_TUNE_LEARNED) {
                 // tune the shape as a single-grid plan
                 offt_plan_s tmp;
@@ -529,12 +528,6 @@ static int choose_many(offt_plan_s* p, const offt_opts& o) {
                 const int rc = select_plan(&tmp, o2, &c, nullptr);
                 for (void* d : tmp.allocs) (void)hipFree(d);
                 if (rc != OFFT_SUCCESS) return rc;
-                // a plan cache or the selector may name a kernel the executors do not hold
-                for (int ax = 0; ax < 3; ++ax)
-                    if (c.k[ax] && c.k[ax]->extra) {
-                        c.k[ax] = rules.k[ax];
-                        c.logW[ax] = rules.logW[ax];
-                    }
             }
             it = chosen.emplace(key, c).first;
         }

@@ -41,11 +41,13 @@ static std::string device_name() {
     return n;
 }
 
-std::string cache_key(int dtype, const int64_t dims[3], int64_t batch, int layout) {
+// rules: tuned among the kernels of the radix-sequence rules only and pass by
+// pass (the grids of many-plans), so that the entry is no single plan's.
+static std::string cache_key(const offt_plan_s* p, bool rules) {
     char buf[256];
-    snprintf(buf, sizeof buf, "dtype=%d dims=%lldx%lldx%lld batch=%lld dev=%s%s", dtype, (long long)dims[0],
-             (long long)dims[1], (long long)dims[2], (long long)batch, device_name().c_str(),
-             layout == OFFT_LAYOUT_REVERSED ? " layout=cba" : "");
+    snprintf(buf, sizeof buf, "dtype=%d dims=%lldx%lldx%lld batch=%lld dev=%s%s%s", p->dtype, (long long)p->dims[0],
+             (long long)p->dims[1], (long long)p->dims[2], (long long)p->batch, device_name().c_str(),
+             p->layout == OFFT_LAYOUT_REVERSED ? " layout=cba" : "", rules ? " kernels=rules" : "");
     return buf;
 }
 
@@ -72,24 +74,34 @@ static std::string plan_to_string(const offt_plan_s* p, const PlanChoice& c, con
     return s;
 }
 
-// Returns OFFT_SUCCESS and fills *c (and *cb) when the cache holds a usable entry.
+// Returns OFFT_SUCCESS and fills *c (and *cb) when the cache holds a usable
+// entry.  A many-plan's grid takes its own entries first, then a single plan's
+// whose kernels all belong to the rules (files written before the two kinds of
+// entries were told apart); another one is a miss: with some of its axes on
+// other kernels it would be a plan that nobody timed.
 static int cache_lookup(const char* path, const offt_plan_s* p, PlanChoice* c, PlanChoice* cb) {
     std::ifstream f(path);
     if (!f) return OFFT_ERR_IO;
-    const std::string key = cache_key(p->dtype, p->dims, p->batch, p->layout);
+    const std::string key = cache_key(p, false), rules_key = cache_key(p, true);
     std::string line;
     int rc = OFFT_ERR_IO;
+    bool own = false;
     while (std::getline(f, line)) {
         const size_t t1 = line.find('\t');
-        if (t1 == std::string::npos || line.compare(0, t1, key) != 0 || t1 != key.size()) continue;
+        if (t1 == std::string::npos) continue;
+        const bool rules = p->rules_only && line.compare(0, t1, rules_key) == 0;
+        if (!rules && (own || line.compare(0, t1, key) != 0)) continue;
         const size_t t2 = line.find('\t', t1 + 1);
         const std::string plan = line.substr(t1 + 1, t2 == std::string::npos ? std::string::npos : t2 - t1 - 1);
         PlanChoice pc, pcb;
-        if (plan_from_string(p, plan, &pc, &pcb)) {
-            *c = pc;   // the latest valid entry wins
-            if (cb) *cb = pcb;
-            rc = OFFT_SUCCESS;
-        }
+        if (!plan_from_string(p, plan, &pc, &pcb)) continue;
+        bool held = true;
+        for (int ax = 0; ax < 3 && p->rules_only; ++ax) held = held && !(pc.k[ax] && pc.k[ax]->extra);
+        if (!held) continue;
+        *c = pc;   // the latest valid entry wins
+        if (cb) *cb = pcb;
+        own = rules;
+        rc = OFFT_SUCCESS;
     }
     return rc;
 }
@@ -98,7 +110,7 @@ static void cache_store(const char* path, const offt_plan_s* p, const PlanChoice
                         float ms) {
     std::ofstream f(path, std::ios::app);
     if (!f) return;
-    f << cache_key(p->dtype, p->dims, p->batch, p->layout) << '\t' << plan_to_string(p, c, cb) << '\t' << ms
+    f << cache_key(p, p->rules_only) << '\t' << plan_to_string(p, c, cb) << '\t' << ms
       << '\n';
 }
 
@@ -860,3 +872,28 @@ std::string describe_plan(const offt_plan_s* p) {
 }
 
 }  // namespace offt
+
+using namespace offt;
+
+// Not part of the C ABI: the plan that a single plan, or a many-plan's grid
+// (rules_only), finds in a plan cache; with `store`, its entry is added first
+// (tests).
+extern "C" int offt_test_plan_cache(const char* path, int dtype, const int64_t* dims, int rules_only, const char* store,
+                                    char* buf, size_t n) {
+    offt_plan_s p;
+    p.kind = 1;
+    p.dtype = dtype;
+    memcpy(p.dims, dims, sizeof p.dims);
+    p.batch = 1;
+    p.rules_only = rules_only != 0;
+    PlanChoice c;
+    if (store) {
+        if (!choice_from_string(store, dtype, dims, &c, false)) return OFFT_ERR_BAD_PLAN;
+        cache_store(path, &p, c, c, 1.f);
+    }
+    const int rc = cache_lookup(path, &p, &c, nullptr);
+    if (rc != OFFT_SUCCESS) return rc;
+    const std::string s = choice_to_string(c, dims);
+    snprintf(buf, n, "%s", s.c_str());
+    return (int)s.size();
+}
