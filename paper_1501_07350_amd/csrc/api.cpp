@@ -296,7 +296,7 @@ offt_plan_t offt_plan_ex(int64_t Na, int64_t Nb, int64_t Nc, int dtype, int64_t 
     p->batch = batch;
     p->normalize = opts.normalize_inverse ? 1 : 0;
     p->layout = opts.layout;
-    p->allow_fuse = opts.tune != OFFT_TUNE_FORCED;
+    p->allow_fuse = true;
     hipStream_t s = static_cast<hipStream_t>(opts.stream);
 
     PlanChoice choice = reversed ? default_choice_reversed(dtype, dims, batch) : default_choice(dtype, dims, batch);
@@ -383,7 +383,7 @@ offt_plan_t offt_plan_nd(int ndim, const int64_t* dims, int dtype, int64_t batch
     for (int i = 0; i < ndim; ++i) p->nd_dims[i] = dims[i];
     p->batch = batch;
     p->normalize = opts.normalize_inverse ? 1 : 0;
-    p->allow_fuse = opts.tune != OFFT_TUNE_FORCED;
+    p->allow_fuse = true;
     hipStream_t s = static_cast<hipStream_t>(opts.stream);
     if (opts.tune == OFFT_TUNE_EXHAUSTIVE || opts.tune == OFFT_TUNE_LEARNED) {
         rc = select_plan_nd(p, opts, &choice);

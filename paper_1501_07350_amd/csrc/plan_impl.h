@@ -40,7 +40,7 @@ struct offt_plan_s {
     std::map<int, void*> tw;      // twiddle table per pass length
     std::vector<void*> allocs;    // every device allocation owned by the plan
     std::vector<size_t> alloc_bytes;
-    bool allow_fuse = false;      // passes may run as block kernels (not when the caller names the plan)
+    bool allow_fuse = false;      // passes may run as block kernels (not a many-plan's grids)
     bool rules_only = false;      // tuned without the kernels that only kernel_defaults.txt names
     std::string tune_log;         // how the plan was chosen (for describe)
     offt::ManyState* many = nullptr;
