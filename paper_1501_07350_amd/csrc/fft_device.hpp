@@ -695,11 +695,23 @@ template <typename V> __device__ __forceinline__ void store_io(V* p, V v, bool n
 }
 
 // load_first from g[j * stride] in HBM; one branch on the access mode around
-// all loads.
-template <typename V, int L, int TPL, int R>
+// all loads, or (EACH) one per load.  Which is faster was measured form by
+// form, on grids of 1 to 16 GiB, around all -> per load:
+//   strided lines    complex128, radix 32 first: 1024 points on a stride of 16
+//                    MiB 7.46 -> 7.11 ms, 512 points 709 -> 703 us (b);
+//                    radix 16 first 810 -> 825 us (512^3, pass a); complex64
+//                    389 -> 393 us (450 points), 76.8 -> 79.4 (384)
+//   rows, direct     complex128, 1024 points 5.74 -> 5.56 ms; complex64 2.61,
+//                    2.62 ms
+//   strided lines of transposing passes: 512 points, complex128 938 -> 905 us,
+//                    complex64 498 -> 470
+template <bool EACH, typename V, int L, int TPL, int R>
 __device__ __forceinline__ void load_first_io(StageRegs<V, L, TPL, R>& v, int t, bool act, const V* __restrict__ g,
                                               int64_t stride, bool nt) {
-    if (nt) {
+    if constexpr (EACH) {
+        auto src = [&](int j) { return load_io(g + (int64_t)j * stride, nt); };
+        load_first<V, L, TPL, R>(v, t, act, src);
+    } else if (nt) {
         auto src = [&](int j) { return load_stream(g + (int64_t)j * stride); };
         load_first<V, L, TPL, R>(v, t, act, src);
     } else {
@@ -844,7 +856,7 @@ __device__ __forceinline__ void pass_tile_impl(const PassArgs& a, V* __restrict_
         V* go = out + base;
         LineSink<V, COHERENT> sink{go, M2, ok, nts, cout, scale};
         StageRegs<V, L, TPL, R0> x;
-        load_first_io<V, L, TPL, R0>(x, t, active, g, M2, nt);
+        load_first_io<OVERLAP && R0 * sizeof(V) >= 512, V, L, TPL, R0>(x, t, active, g, M2, nt);
         if constexpr (kTwiddles) twiddles_finish<V, L>(twl, tw0, tw1, tw, tid, tw_first);
         map_first<V, L, TPL, R0>(x, t, active, fix);
         fft_from_regs<V, L, TPL, P, false, false, Rs...>(x, lds + w * LP, twl, t, active, sink);
@@ -864,7 +876,7 @@ __device__ __forceinline__ void pass_tile_impl(const PassArgs& a, V* __restrict_
                 if (ok) store_elem_io<COHERENT>(go + j, fix_out(x, cout, scale), nts);
             };
             StageRegs<V, L, TPL, R0> x;
-            load_first_io<V, L, TPL, R0>(x, t, active, g, 1, nt);
+            load_first_io<OVERLAP && sizeof(V) == 16, V, L, TPL, R0>(x, t, active, g, 1, nt);
             if constexpr (kTwiddles) twiddles_finish<V, L>(twl, tw0, tw1, tw, tid, tw_first);
             map_first<V, L, TPL, R0>(x, t, active, fix);
             fft_from_regs<V, L, TPL, 1, false, false, Rs...>(x, line, twl, t, active, sink);
@@ -1099,7 +1111,7 @@ __device__ __forceinline__ void pass_tile_transpose(const PassArgs& a, V* __rest
     } else {
         const V* g = in + base;
         StageRegs<V, L, TPL, R0> x;
-        load_first_io<V, L, TPL, R0>(x, t, active, g, M2, nt);
+        load_first_io<true, V, L, TPL, R0>(x, t, active, g, M2, nt);
         if constexpr (kTwiddles) twiddles_finish<V, L>(twl, tw0, tw1, tw, tid, tw_first);
         map_first<V, L, TPL, R0>(x, t, active, fix);
         if constexpr (P == 1) {
