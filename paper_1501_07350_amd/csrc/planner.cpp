@@ -1073,9 +1073,12 @@ static int block_threads(int dtype, int A, int B, int C, int naxes, int64_t bloc
 //                  64 x 32^3 complex128 37.7 -> 29.5 us
 //   one block per  8 x 100^3 complex64 65.8 -> 75.4 us (in the Infinity Cache),
 //   CU             64 of them 617 -> 549 us, 128^4 2.97 -> 2.80 ms (streaming);
-//                  128^3 alone 35.6 -> 27.3 us, 8 of them equal; 65 to 113
-//                  planes of 36 to 100 x 72 to 240: 0.72 to 0.98 of the
-//                  separate passes' speed
+//                  128^3 alone 35.6 -> 27.3 us, 8 of them equal; fewer planes
+//                  alone, speed against separate passes: 64, 80 and 108 of 100 x
+//                  100 complex64 1.00, 1.05, 1.15, of 128 x 128 0.92, 1.01,
+//                  1.19, of 90 x 90 complex128 0.98, 1.07, 1.19; with threads
+//                  idle in a round 64, 108, 128 and 160 of 100 x 120 complex64
+//                  0.79, 0.94, 0.98, 1.03, of 72 x 150 0.76, 0.91, 0.95, 1.02
 //   few blocks     12 x 150 x 60 complex64 14.3 -> 16.4 us; a plane to a CU with
 //                  three-stage lines, 125^3 complex64 33.5 -> 36.2 us, but
 //                  250 x 125^2 44.7 -> 41.2 us
@@ -1121,10 +1124,16 @@ static int fuse_rule(int dtype, int64_t A, int64_t B, int64_t C, int64_t grids, 
     if (!few(B * C * es, planes, streamed ? 100 * es : 2048)) return 0;
     const int sb = block_case_of_length(dtype, B)->nstages, sc = block_case_of_length(dtype, C)->nstages;
     if (sb > 2 && planes * B * C * es > (int64_t(64) << 20)) return 0;
-    if (lds <= kTwoPerCu ? (B * C <= 4096 || planes >= 64)
-                         : ((planes >= (std::max(sb, sc) <= 2 ? 128 : 192) && planes <= kCUs) || streamed))
-        return launches(1, 2, planes) ? 2 : 0;
-    return 0;
+    if (lds <= kTwoPerCu) {
+        if (B * C > 4096 && planes < 64) return 0;
+    } else if (!streamed) {
+        // lines that fill three quarters of each round of threads
+        const int64_t t = block_threads(dtype, 1, (int)B, (int)C, 2, planes, false, lds_max);
+        const auto full = [&](int64_t w) { return 4 * w >= 3 * ((w + t - 1) / t * t); };
+        const bool busy = full(B * block_case_of_length(dtype, C)->tpl) && full(C * block_case_of_length(dtype, B)->tpl);
+        if (planes < (std::max(sb, sc) > 2 ? 192 : busy ? 80 : 128) || planes > kCUs) return 0;
+    }
+    return launches(1, 2, planes) ? 2 : 0;
 }
 
 void set_fuse(PassPlan* ps, int n) {

@@ -59,8 +59,10 @@ def test_a_launch_holds_fewer_than_2_32_threads(dtype):
 
 
 def test_few_planes_that_fill_a_cu():
-    # 128 x 128 complex64 fills a CU's LDS: from 128 planes to 256, or streaming
-    assert fused(127, 128, 128, 1, C64) == 0 and fused(128, 128, 128, 1, C64) == 2
+    # 128 x 128 complex64 fills a CU's LDS and its threads: from 80 planes to
+    # 256, or streaming; 100 x 120 leaves threads idle: from 128
+    assert fused(79, 128, 128, 1, C64) == 0 and fused(80, 128, 128, 1, C64) == 2
+    assert fused(127, 100, 120, 1, C64) == 0 and fused(128, 100, 120, 1, C64) == 2
     assert fused(1, 128, 128, 257, C64) == 0 and fused(1, 128, 128, 4096, C64) == 2
 
 
