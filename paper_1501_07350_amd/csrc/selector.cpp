@@ -30,6 +30,16 @@ namespace offt {
 
 static const int kOrders[6][3] = {{2, 1, 0}, {2, 0, 1}, {1, 2, 0}, {1, 0, 2}, {0, 2, 1}, {0, 1, 2}};
 
+// Axes of a plan that run in block launches.
+static int fused_axes(const PlanChoice& c, const int64_t dims[3], int64_t batch) {
+    PassPlan passes[3];
+    const int n = build_passes(c, dims, batch, passes);
+    set_fuse(passes, n);
+    int f = 0;
+    for (int i = 0; i < n; ++i) f += passes[i].fuse;
+    return f;
+}
+
 std::vector<PlanChoice> selector_candidates(int dtype, const int64_t dims[3], int64_t batch, bool rules_only) {
     std::vector<PlanChoice> out = candidate_choices(dtype, dims, batch, rules_only);
     if (out.empty()) return out;
@@ -42,6 +52,16 @@ std::vector<PlanChoice> selector_candidates(int dtype, const int64_t dims[3], in
         PlanChoice c = base;
         c.io[ax] = resolve_stream(base.io[ax], bytes) ? kIoCached : kIoStream;
         out.push_back(c);
+    }
+    // the features do not say which passes run as one block launch, and the
+    // network's training data had none: where the heuristic's plan has such a
+    // launch, candidates without it are left out (64^3 complex64: order abc,
+    // three launches, 14.0 us; the heuristic's two 11.6)
+    if (!rules_only) {
+        const int f = fused_axes(base, dims, batch);
+        out.erase(std::remove_if(out.begin() + 1, out.end(),
+                                 [&](const PlanChoice& c) { return fused_axes(c, dims, batch) < f; }),
+                  out.end());
     }
     return out;
 }

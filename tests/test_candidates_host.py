@@ -34,3 +34,19 @@ def test_first_candidate_is_the_batch_default(gk, prec, dtype, batch, cls):
              for ax, n in zip("abc", shape)] for f in fields]
     assert all(same[0])
     assert all(sum(s) >= 2 for s in same)      # the others change one axis's kernel at most
+
+
+@pytest.mark.parametrize("shape,dtype", [((64, 64, 64), 1), ((48, 48, 48), 0), ((16, 12, 18), 1)])
+def test_candidates_keep_the_block_launch(shape, dtype):
+    """Where the default runs passes c and b (and a) as blocks, every candidate
+    does: c before b, with the default's kernels."""
+    plans, feats = selector.candidates(shape, 1, dtype)
+    fields = [dict(f.split("=", 1) for f in p.split(";")) for p in plans]
+    assert len(plans) > 4 and len(feats) == len(plans)
+    assert all(f["order"].startswith("cb") or f["order"] == "acb" for f in fields)
+    assert all(f[ax].split("/")[0] == fields[0][ax].split("/")[0] for f in fields for ax in "bc")
+
+
+def test_candidates_of_separate_passes_have_every_order():
+    plans, _ = selector.candidates((40, 450, 500), 1, 1)
+    assert len({p.split(";")[0] for p in plans}) == 6
