@@ -47,3 +47,10 @@ def test_width_by_row_alignment(gk, L, listed, columns):
     got = _fields(offt.default_plan_string((1000, L, columns), DTYPES["f32"]))["b"].split("/")
     assert got[0] == spec[0]
     assert int(got[1]) == int(spec[1]) // (2 if listed and columns * 8 % 128 == 0 else 1)
+
+
+def test_large_transposing_pass_of_512():
+    """Reversed 512^3, complex128: the transposing pass of a large grid has two
+    stages (three took 1.09 of their time)."""
+    plan = offt.plan_string((512, 512, 512), DTYPES["f64"], "cba")
+    assert [_fields(p)["a"] for p in plan.split("|")] == ["16x16x2/16/p2"] * 2
