@@ -314,9 +314,10 @@ constexpr int64_t kTableMinLines = 256;
 // x 3 228 against 254 us, 256^3 x 2 237 against 260, 144^3 x 9 202 against
 // 201), at 261 MiB 1.52; complex128, boxes of 12 shapes, 0.91, 0.96, 0.94 and
 // 1.06 at 160, 208, 256 and 330 MiB.  A complex64 plan with a transposing pass
-// also fills a workspace; three such plans run in turn took 254 us with the
-// third class and 272 with the second (256 x 320 x 384), one plan alone 238
-// and 228: its line lies at 192 MiB.
+// also fills a workspace, and its line lies at 192 MiB: over 14 boxes of 198
+// to 253 MiB the third class took 0.957 of the second's time in the mean where
+// three plans ran in turn (0.89 to 0.97 on eleven, 1.01 to 1.12 on three) and
+// 1.006 where one plan ran alone (0.95 to 1.06, backward 0.89 to 1.06).
 constexpr int64_t kSmallGridBytes = int64_t(8) << 20;
 constexpr int64_t kLargeTransposedBytes = int64_t(192) << 20;
 
