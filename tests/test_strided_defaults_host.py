@@ -50,7 +50,7 @@ def test_width_by_row_alignment(gk, L, listed, columns):
 
 
 def test_large_transposing_pass_of_512():
-    """Reversed 512^3, complex128: the transposing pass of a large grid has two
-    stages (three took 1.09 of their time)."""
+    """Reversed 512^3, complex128: the transposing pass of a large grid takes
+    16 x 16 x 2 (8 x 8 x 8 took 1.09 of its time; the width is the device's)."""
     plan = offt.plan_string((512, 512, 512), DTYPES["f64"], "cba")
-    assert [_fields(p)["a"] for p in plan.split("|")] == ["16x16x2/16/p2"] * 2
+    assert [_fields(p)["a"].split("/")[0] for p in plan.split("|")] == ["16x16x2"] * 2
