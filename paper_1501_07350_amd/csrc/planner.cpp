@@ -326,6 +326,25 @@ constexpr int64_t kLargeTransposedBytes = int64_t(192) << 20;
 // what was measured).
 constexpr int64_t kCacheLine = 128;
 
+// Whether streaming strided lines, whose rows lie `row` bytes apart, take half
+// of a tile width of `width` bytes.
+//   below 2 MiB     where rows are whole cache lines (or less than one)
+//   from 2 MiB on   (each row of a tile on a page of its own) complex64 where
+//                   the half still spans two cache lines, complex128 there
+//                   also only at powers of two, whose rows fall on the same
+//                   channels
+// Time with the width against half of it, first axes of all listed lengths
+// (means; halves of 256 bytes, of 128 bytes), complex64: 15 strides of 0.6 to
+// 1.95 MiB 1.01 to 1.07, 1.04 to 1.09; 2 and 4 MiB 1.07, 0.87 to 0.92; other
+// strides to 7.6 MiB 1.00 to 1.04, 0.95 to 1.04.  complex128: six strides of
+// 1.2 to 1.98 MiB 1.02 to 1.06, 1.03 to 1.10; 2 and 8 MiB 1.08 and 1.03, 0.91
+// and 0.88; 13 others to 15 MiB 0.96 to 1.02, 0.90 to 1.01.
+static bool halves_width(int64_t row, int64_t width, int64_t es) {
+    constexpr int64_t kPage = int64_t(2) << 20;
+    if (row % kCacheLine != 0 && row >= kCacheLine) return false;
+    return row < kPage || (width >= 4 * kCacheLine && (es == 8 || (row & (row - 1)) == 0));
+}
+
 // The measured default kernel and tile width of a pass over `lines` lines of
 // length L and element stride m2 in a batch of grids of `bytes`; null where the
 // table has none.
@@ -333,14 +352,14 @@ static const KernelEntry* table_kernel(int dtype, int L, LineKind kind, int64_t 
                                        int* logW) {
     if (lines < kTableMinLines) return nullptr;
     const int cls = bytes <= kSmallGridBytes ? 0 : (bytes <= kStreamMinBytes ? 1 : 2);
-    const int64_t row = m2 * (int64_t)elem_size(dtype);
+    const int64_t es = (int64_t)elem_size(dtype), row = m2 * es;
     if (cls == 2 && kind == kStrided && row < (L < 512 ? kCacheLine : kCacheLine / 4)) return nullptr;
     for (const KernelDefault& d : kKernelDefaults) {
         if (d.dtype != dtype || d.kind != kind || d.L != L) continue;
         AxisSpec sp;
         const KernelEntry* k = parse_axis_spec(d.spec[cls], &sp) ? find_kernel(dtype, L, sp) : nullptr;
         if (!k) return nullptr;
-        if (cls == 2 && d.half && (row % kCacheLine == 0 || row < kCacheLine)) sp.W /= 2;
+        if (cls == 2 && d.half && halves_width(row, sp.W * es, es)) sp.W /= 2;
         *logW = fit_logW(k, ilog2(sp.W), dtype, kind == kTransposing ? kGeomTranspose : kGeomNatural);
         return k;
     }
@@ -1229,7 +1248,10 @@ using namespace offt;
 extern "C" {
 
 // Not part of the C ABI: the block rule and the threads of a block launch for
-// a device with lds_max bytes of LDS per workgroup (tests).
+// a device with lds_max bytes of LDS per workgroup, and the rule of the width
+// of streaming strided lines (tests).
+int offt_test_halves_width(int64_t row, int64_t width, int64_t es) { return halves_width(row, width, es); }
+
 int offt_test_fuse_rule(int dtype, int64_t A, int64_t B, int64_t C, int64_t grids, int64_t lds_max) {
     return fuse_rule(dtype, A, B, C, grids, lds_max);
 }

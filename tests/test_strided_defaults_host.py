@@ -1,4 +1,5 @@
 """Default kernels of streaming strided passes by the stride, host side."""
+import ctypes
 import importlib.util
 import os
 
@@ -54,3 +55,18 @@ def test_large_transposing_pass_of_512():
     16 x 16 x 2 (8 x 8 x 8 took 1.09 of its time; the width is the device's)."""
     plan = offt.plan_string((512, 512, 512), DTYPES["f64"], "cba")
     assert [_fields(p)["a"].split("/")[0] for p in plan.split("|")] == ["16x16x2"] * 2
+
+
+@pytest.mark.parametrize("prec,m,half_row,half", [
+    ("f64", (360, 360), 256, True), ("f64", (480, 500), 256, False),    # complex128: the line at 2 MiB
+    ("f64", (512, 256), 256, True), ("f64", (400, 400), 256, False),    # above it at powers of two only
+    ("f64", (512, 256), 128, False), ("f64", (360, 360), 128, True),    # halves of 128 bytes below it only
+    ("f32", (512, 500), 128, True), ("f32", (512, 512), 128, False),
+    ("f32", (512, 512), 256, True), ("f32", (800, 600), 256, True),
+    ("f32", (801, 601), 256, False), ("f32", (1, 5), 256, True)])       # rows of partial lines
+def test_width_by_row_distance(prec, m, half_row, half):
+    """Streaming strided lines whose rows lie m elements apart: half of the
+    width or not."""
+    es = 16 if prec == "f64" else 8
+    assert bool(offt._lib.load().offt_test_halves_width(ctypes.c_int64(m[0] * m[1] * es), ctypes.c_int64(2 * half_row),
+                                                        ctypes.c_int64(es))) == half
