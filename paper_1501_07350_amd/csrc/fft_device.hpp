@@ -696,15 +696,19 @@ template <typename V> __device__ __forceinline__ void store_io(V* p, V v, bool n
 
 // load_first from g[j * stride] in HBM; one branch on the access mode around
 // all loads, or (EACH) one per load.  Which is faster was measured form by
-// form, on grids of 1 to 16 GiB, around all -> per load:
+// form, around all -> per load (six runs of each in turn, which differ by 1%;
+// means over the table's lengths at 40, 200 and 400 MiB):
 //   strided lines    complex128, radix 32 first: 1024 points on a stride of 16
-//                    MiB 7.46 -> 7.11 ms, 512 points 709 -> 703 us (b);
-//                    radix 16 first 810 -> 825 us (512^3, pass a); complex64
-//                    389 -> 393 us (450 points), 76.8 -> 79.4 (384)
-//   rows, direct     complex128, 1024 points 5.74 -> 5.56 ms; complex64 2.61,
-//                    2.62 ms
-//   strided lines of transposing passes: 512 points, complex128 938 -> 905 us,
-//                    complex64 498 -> 470
+//                    MiB 7.47 -> 7.18 ms, 512 points 846 -> 838 us; other
+//                    radices and complex64 the means are 1.002 to 1.004 of it
+//   rows, direct     complex128 on 2 to 16 GiB: 1024 points 5.83 -> 5.62 ms, 512
+//                    755 -> 746 us, 600 1201 -> 1177; below, means of 1.004 to
+//                    1.009; complex64 equal on large grids, below 1.000 to 1.007
+//   strided lines of transposing passes: complex64, radix 8 first 499 -> 470 us
+//                    (512^3), 998 -> 961 (512 x 512 x 1024), the mean is equal;
+//                    other radices 100 -> 107 (300^3), 89 -> 94 (400 x 256 x
+//                    300), 1310 -> 1358 (1024 x 512 x 512), means of 1.005 to
+//                    1.011; complex128 within 1% either way (512^3)
 template <bool EACH, typename V, int L, int TPL, int R>
 __device__ __forceinline__ void load_first_io(StageRegs<V, L, TPL, R>& v, int t, bool act, const V* __restrict__ g,
                                               int64_t stride, bool nt) {
@@ -1111,7 +1115,7 @@ __device__ __forceinline__ void pass_tile_transpose(const PassArgs& a, V* __rest
     } else {
         const V* g = in + base;
         StageRegs<V, L, TPL, R0> x;
-        load_first_io<true, V, L, TPL, R0>(x, t, active, g, M2, nt);
+        load_first_io<R0 == 8, V, L, TPL, R0>(x, t, active, g, M2, nt);
         if constexpr (kTwiddles) twiddles_finish<V, L>(twl, tw0, tw1, tw, tid, tw_first);
         map_first<V, L, TPL, R0>(x, t, active, fix);
         if constexpr (P == 1) {
