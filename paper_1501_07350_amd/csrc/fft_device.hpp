@@ -703,12 +703,15 @@ template <typename V> __device__ __forceinline__ void store_io(V* p, V v, bool n
 //                    radices and complex64 the means are 1.002 to 1.004 of it
 //   rows, direct     complex128 on 2 to 16 GiB: 1024 points 5.83 -> 5.62 ms, 512
 //                    755 -> 746 us, 600 1201 -> 1177; below, means of 1.004 to
-//                    1.009; complex64 equal on large grids, below 1.000 to 1.007
+//                    1.009 (and slab by slab, 512^3 tuned 2074 -> 2084 us), so
+//                    from kEachRowBytes on; complex64 equal on large grids,
+//                    below 1.000 to 1.007
 //   strided lines of transposing passes: complex64, radix 8 first 499 -> 470 us
 //                    (512^3), 998 -> 961 (512 x 512 x 1024), the mean is equal;
 //                    other radices 100 -> 107 (300^3), 89 -> 94 (400 x 256 x
 //                    300), 1310 -> 1358 (1024 x 512 x 512), means of 1.005 to
 //                    1.011; complex128 within 1% either way (512^3)
+constexpr int64_t kEachRowBytes = int64_t(1) << 30;
 template <bool EACH, typename V, int L, int TPL, int R>
 __device__ __forceinline__ void load_first_io(StageRegs<V, L, TPL, R>& v, int t, bool act, const V* __restrict__ g,
                                               int64_t stride, bool nt) {
@@ -880,7 +883,10 @@ __device__ __forceinline__ void pass_tile_impl(const PassArgs& a, V* __restrict_
                 if (ok) store_elem_io<COHERENT>(go + j, fix_out(x, cout, scale), nts);
             };
             StageRegs<V, L, TPL, R0> x;
-            load_first_io<OVERLAP && sizeof(V) == 16, V, L, TPL, R0>(x, t, active, g, 1, nt);
+            if (OVERLAP && sizeof(V) == 16 && a.nlines * (int64_t)(L * sizeof(V)) >= kEachRowBytes)
+                load_first_io<true, V, L, TPL, R0>(x, t, active, g, 1, nt);
+            else
+                load_first_io<false, V, L, TPL, R0>(x, t, active, g, 1, nt);
             if constexpr (kTwiddles) twiddles_finish<V, L>(twl, tw0, tw1, tw, tid, tw_first);
             map_first<V, L, TPL, R0>(x, t, active, fix);
             fft_from_regs<V, L, TPL, 1, false, false, Rs...>(x, line, twl, t, active, sink);
