@@ -76,7 +76,8 @@ typedef struct offt_opts {
     int tune;                 /* OFFT_TUNE_* (default NONE) */
     int reps;                 /* timed runs per candidate when tuning (default 2, after 1 warm-up) */
     int normalize_inverse;    /* 1: backward multiplies by 1/(Na Nb Nc) (default 0) */
-    const char* forced_plan;  /* plan string for OFFT_TUNE_FORCED (format of offt_plan_describe) */
+    const char* forced_plan;  /* plan string for OFFT_TUNE_FORCED (format of offt_plan_describe); passes that
+                                 fit a CU's LDS together run as one launch, as in the plan it describes */
     const char* cache_path;   /* plan cache file for tuned plans, or NULL */
     const char* weights_path; /* learned-selector weights for OFFT_TUNE_LEARNED, or NULL */
     void* stream;             /* hipStream_t for tuning runs (NULL = null stream) */
@@ -265,7 +266,8 @@ int64_t offt_workspace_bytes(offt_plan_t p);
 int offt_last_error(void);
 const char* offt_error_string(int code);
 
-/* Plan string of the heuristic plan (OFFT_TUNE_NONE) for one grid shape,
+/* Plan string of the heuristic plan (OFFT_TUNE_NONE) for one grid shape and
+ * batch 1 (a batch may have another: kernels follow the batch's bytes),
  * written like offt_plan_describe.  Needs no device: the per-workgroup LDS
  * limit is the current device's when one is visible, 64 KiB otherwise.
  * Returns the full string length or INVALID_ARG / UNSUPPORTED_SIZE. */

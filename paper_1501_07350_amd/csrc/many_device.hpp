@@ -221,7 +221,8 @@ __device__ __forceinline__ void many_level_body(const ManyArgs& a, int64_t tile_
 // atomics serialise on their address, and a shared tile queue costs more
 // than the imbalance it removes (consecutive tiles come from one segment, so
 // a round-robin deal gives every workgroup near-equal work).  The tile code
-// is one out-of-line call, so the loop keeps only its own few values live.
+// is inlined and reads its thread index through tile_thread_index<LOOPED>, so
+// that no case's index math stays live around the loop.
 // Tiles use plain stores; the barrier makes them visible across XCDs: every
 // thread waits for its stores, then one thread releases at agent scope (L2
 // write-back), arrives, waits for all workgroups, and acquires (L2
