@@ -984,7 +984,8 @@ def summarize_nd(d: str, log: str, command: str, steps: int, warmup: int) -> str
     --kernel-trace run of `--nd-only` (plans from the plan cache, so every
     pass dispatch belongs to a timed or warm-up transform): for each grid,
     the tuned plan and then the heuristic plan, `warmup + steps` transforms
-    of one dispatch per axis in the plan's pass order."""
+    of one dispatch per axis in the plan's pass order; a block kernel stands
+    for two passes."""
     res = None
     for line in open(log):
         if line.startswith("{"):
@@ -993,8 +994,8 @@ def summarize_nd(d: str, log: str, command: str, steps: int, warmup: int) -> str
         raise RuntimeError(f"no result line in {log}")
     trace = _read_csv(_find(d, "kernel_trace.csv"))
     trace.sort(key=lambda r: int(r["Dispatch_Id"]))
-    disp = [(int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e3 for r in trace
-            if "fft_pass_kernel" in r["Kernel_Name"]]
+    disp = [((int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e3, "fft_block_" in r["Kernel_Name"]) for r in trace
+            if "fft_pass_kernel" in r["Kernel_Name"] or "fft_block_" in r["Kernel_Name"]]
     lines = ["# rocprofv3 kernel trace of the 4- and 5-axis transforms: mean duration per pass over the timed",
              "# transforms (a pass of a slab schedule summed over its slabs' dispatches); GB/s = algorithmic",
              "# 2*N*s bytes per pass / duration",
@@ -1012,18 +1013,27 @@ def summarize_nd(d: str, log: str, command: str, steps: int, warmup: int) -> str
             npass = len(pass_keys(plan))
             per = [[0.0] * steps for _ in range(npass)]
             seq = pass_launches(plan, r["shape"][0])
+            merged = set()   # passes that ran in the launch of the one before
             for st in range(warmup + steps):
+                block = False
                 for i in seq:
+                    if block:
+                        merged.add(i)
+                        block = False
+                        continue
                     if k >= len(disp):
                         raise RuntimeError(f"the trace holds {len(disp)} pass dispatches, fewer than expected")
+                    us, block = disp[k]
                     if st >= warmup:
-                        per[i][st - warmup] += disp[k]
+                        per[i][st - warmup] += us
                     k += 1
             total = 0.0
             for i in range(npass):
+                if i in merged:
+                    continue
                 m = sum(per[i]) / len(per[i])
                 total += m
-                label = pass_label(plan, i)
+                label = pass_label(plan, i) + (f" + {pass_label(plan, i + 1)}" if i + 1 in merged else "")
                 lines.append(f"  pass {i} {label:<16} {m:9.2f} us  {2.0 * N * s / (m * 1e3):7.1f} GB/s")
             lines.append(f"  summed pass time {total:.1f} us")
     if k != len(disp):

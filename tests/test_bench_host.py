@@ -2,6 +2,7 @@
 traces (no GPU)."""
 import csv
 import importlib.util
+import json
 import os
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -241,3 +242,20 @@ def test_roofline_and_copy_ceilings_of_a_slab_schedule():
     c = b.copy_ceilings(res)
     assert [x["pass"] for x in c] == ["a=8/8", "b=8/8+c=8/8;slab=3"]
     assert c[1]["copy_ms"] == 1.2 and c[1]["pass_gbs"] == round(2e9 / 1.5e6, 1) and c[1]["frac_of_copy"] == 0.8
+
+
+def test_nd_trace_summary_with_block_kernels(tmp_path):
+    """A block kernel stands for two passes, first or within the transform."""
+    steps, warmup = 2, 1
+    P, B = "void offt::fft_pass_kernel<...>(offt::PassArgs)", "offt::(anonymous namespace)::fft_block_long_f32(offt::BlockArgs)"
+    per = {"tuned": [(P, 500000), (B, 900000), (P, 600000)], "heuristic": [(B, 800000), (P, 700000), (P, 750000)]}
+    write_trace(str(tmp_path / "run_kernel_trace.csv"),
+                [(n, d, 1000) for which in ("tuned", "heuristic") for _ in range(steps + warmup) for n, d in per[which]])
+    log = tmp_path / "nd.log"
+    plans = {"tuned": "order=bdca;a=8/64;b=8/64;c=8/64;d=8/16", "heuristic": "order=dcba;a=8/64;b=8/64;c=8/64;d=8/16"}
+    log.write_text(json.dumps({"nd": [{"shape": [8, 8, 8, 8], "dtype": "f32",
+                                       **{k: {"ms": 2.0, "plan": p} for k, p in plans.items()}}]}) + "\n")
+    lines = [ln.split() for ln in load_bench().summarize_nd(str(tmp_path), str(log), "cmd", steps, warmup).splitlines()]
+    got = [(ln[1], " ".join(ln[2:-4]), float(ln[-4])) for ln in lines if ln[0] == "pass"]
+    assert got == [("0", "b=8/64", 500.0), ("1", "d=8/16 + c=8/64", 900.0), ("3", "a=8/64", 600.0),
+                   ("0", "d=8/16 + c=8/64", 800.0), ("2", "b=8/64", 700.0), ("3", "a=8/64", 750.0)]
