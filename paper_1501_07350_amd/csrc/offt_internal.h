@@ -91,6 +91,7 @@ struct PassPlan {
     // block kernel (fft_block.hpp): this pass and the next fuse - 1 run as one
     // launch over blocks of `fuse` axes when a call covers them all; 0: alone
     int fuse = 0;
+    int block_threads[2] = {0, 0};   // threads of that launch, its stores cached and streamed
     // a strided pass restricted to one column block (PassArgs): lines per
     // m1 (0: M2), log2 of the block width (-1: none), row length, first column
     int64_t lpm = 0;

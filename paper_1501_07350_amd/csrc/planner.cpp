@@ -1167,7 +1167,10 @@ void set_fuse(PassPlan* ps, int n) {
         const bool whole = a && a->mode == 1 && !a->slab && !a->col && a->k && a->M2 == b.M2 * b.L &&
                            b.M1 == a->M1 * a->L && block_case(a->k) >= 0;
         const int f = fuse_rule(c.k->dtype, whole ? a->L : 1, b.L, c.L, whole ? a->M1 : b.M1);
-        if (f > 1) ps[i].fuse = f;
+        if (f < 2) continue;
+        ps[i].fuse = f;
+        for (const bool st : {false, true})
+            ps[i].block_threads[st] = block_threads(c.k->dtype, f == 3 ? a->L : 1, b.L, c.L, f, ps[i + f - 1].M1, st);
     }
 }
 
@@ -1197,7 +1200,7 @@ hipError_t launch_block(const PassPlan* ps, const void* in, void* out, int conj_
     const int dtype = ps[0].k->dtype;
     const int64_t lds = block_lds_elems(a.A, a.B, a.C) * (int64_t)elem_size(dtype);
     if (lds > lds_limit()) return hipErrorInvalidValue;
-    const int threads = block_threads(dtype, a.A, a.B, a.C, f, blocks, a.stream_out != 0);
+    const int threads = ps[0].block_threads[a.stream_out != 0];
     const BlockKernel* bk = block_kernel_for(dtype, std::max(std::max(a.A, a.B), a.C));
     if (threads < 1 || blocks > int64_t(0xffffffffu) / threads) return hipErrorInvalidValue;
     return bk->launch(a, blocks, threads, (size_t)lds, s);
